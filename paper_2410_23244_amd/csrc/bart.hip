@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "predict.hpp"
 #include "sweep.hpp"
 
 using namespace bart;
@@ -46,7 +47,7 @@ struct Layout {
   int64_t n_pad;
   int32_t nchain;
   int32_t gcap;  // workgroups per chain the mailboxes are sized for
-  size_t resid, idx, axis, cut, leaf, count, prop, z, ctl, pub, latent, chain_bytes;
+  size_t resid, idx, axis, cut, leaf, count, prop, z, ctl, pub, latent, prog, chain_bytes;
   size_t n_cuts, nz_list, nz_rank, ybin, args, args_static, total;
 };
 
@@ -109,6 +110,7 @@ Layout make_layout(const bart_config &c) {
   L.ctl = take(sizeof(Ctl));
   L.pub = take(sizeof(uint64_t) * 2 * L.gcap * kStride);
   L.latent = take(c.probit ? sizeof(float) * L.n_pad : 0);
+  L.prog = take(sizeof(PredGroup) * ((m + kPredTrees - 1) / kPredTrees));
   L.chain_bytes = o;
   o = L.chain_bytes * L.nchain;
   L.n_cuts = take(sizeof(int32_t) * c.p);
@@ -331,79 +333,6 @@ __global__ void k_recount(const uint8_t *idx, int64_t ldi, int ib, int32_t *coun
     if (hist[k]) atomicAdd(&count[(int64_t)j * 2 * H + k], hist[k]);
 }
 
-// f(x) = offset + sum_j g(x; T_j, M_j): Algorithm 1 per tree (loop over the
-// levels with a reached-leaf flag), fp64 sum in tree order.  Trees are staged
-// through LDS in tiles of kPredNodes heap slots; every thread follows its
-// point through kPredIlp trees at once so their predictor-byte gathers
-// overlap.  blockIdx.y = chain: its trees sit chain_bytes further on, its
-// outputs nt further on.  ACC: add f and f^2 (fp64) to sum and sumsq instead
-// of writing fp32(f) to out.
-constexpr int kPredBlock = 256;
-constexpr int kPredNodes = 2048;  // heap slots per LDS tile (axis u16 + cut u8 + 2 leaves f32: 22 KB)
-constexpr int kPredIlp = 8;
-
-template <bool ACC>
-__global__ void __launch_bounds__(kPredBlock)
-    k_predict(const uint8_t *Xt, int64_t ldx, int64_t nt, int p, const uint16_t *axis0,
-              const uint8_t *cut0, const float *leaf0, int m, int D, int H, double offset,
-              size_t chain_bytes, float *out0, double *sum0, double *sumsq0) {
-  __shared__ uint16_t s_ax[kPredNodes];
-  __shared__ uint8_t s_ct[kPredNodes];
-  __shared__ float s_lf[2 * kPredNodes];
-  const int t = threadIdx.x;
-  const int64_t i = blockIdx.x * (int64_t)kPredBlock + t;
-  const bool valid = i < nt;
-  const size_t cb = blockIdx.y * chain_bytes;
-  const uint16_t *axis = (const uint16_t *)((const char *)axis0 + cb);
-  const uint8_t *cut = cut0 + cb;
-  const float *leaf = (const float *)((const char *)leaf0 + cb);
-  const int TT = kPredNodes / H;  // trees per tile
-  const uint8_t *xcol = Xt + (valid ? i : 0);
-  double acc = 0.0;
-  for (int j0 = 0; j0 < m; j0 += TT) {
-    const int nt_ = min(TT, m - j0);
-    __syncthreads();
-    for (int q = t; q < nt_ * H; q += kPredBlock) {
-      s_ax[q] = axis[(int64_t)j0 * H + q];
-      s_ct[q] = cut[(int64_t)j0 * H + q];
-    }
-    for (int q = t; q < nt_ * 2 * H; q += kPredBlock) s_lf[q] = leaf[(int64_t)j0 * 2 * H + q];
-    __syncthreads();
-    if (!valid) continue;
-    for (int jj = 0; jj < nt_; jj += kPredIlp) {
-      int index[kPredIlp];
-      bool found[kPredIlp];
-#pragma unroll
-      for (int u = 0; u < kPredIlp; ++u) {
-        index[u] = 1;
-        found[u] = jj + u >= nt_;  // past the tile: nothing to do
-      }
-      for (int lvl = 1; lvl <= D - 1; ++lvl) {
-#pragma unroll
-        for (int u = 0; u < kPredIlp; ++u) {
-          const int base = (jj + u < nt_ ? jj + u : 0) * H;
-          const int a = s_ax[base + index[u]], split = s_ct[base + index[u]];
-          found[u] = found[u] || split == 0;
-          const int xa = found[u] ? 0 : xcol[(int64_t)(a < p ? a : 0) * ldx];
-          index[u] = found[u] ? index[u] : 2 * index[u] + (xa >= split ? 1 : 0);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kPredIlp; ++u)  // tree order
-        if (jj + u < nt_) acc += (double)s_lf[(jj + u) * 2 * H + index[u]];
-    }
-  }
-  if (!valid) return;
-  const int64_t o = blockIdx.y * nt + i;
-  const double f = offset + acc;
-  if (ACC) {
-    sum0[o] += f;
-    sumsq0[o] += f * f;
-  } else {
-    out0[o] = (float)f;
-  }
-}
-
 // Posterior mean and sd of f at each point from the per-chain sums of f and
 // f^2 over n_keep kept sweeps: chain means m_c and variances v_c = E_c[f^2] -
 // m_c^2, pooled by the law of total variance (mean of the v_c plus the
@@ -441,6 +370,7 @@ struct bart_handle {
   const uint8_t *X;
   hipStream_t stream;
   int device;
+  int cus;                 // compute units of the device
   int H, p_nz, V, G, lds;  // V: chunks of 4 observations per thread; G: workgroups per chain
   int nchain;
   bool streamed;           // residuals streamed from HBM instead of kept in registers
@@ -558,6 +488,36 @@ int run_steps(bart_handle *h, int64_t steps, uint64_t seed, bart_trace *trace,
   return BART_OK;
 }
 
+// Prediction: the trees compiled into the workspace, then evaluated.
+template <bool ACC>
+void launch_predict(bart_handle *h, const uint8_t *Xt, int64_t ldx, int64_t nt, double offset,
+                    float *out, double *sum, double *sumsq) {
+  const int m = h->cfg.ntree, p = h->cfg.p, D = h->cfg.max_depth;
+  const int ngroups = (m + kPredTrees - 1) / kPredTrees;
+  const uint16_t *axis = atc<uint16_t>(h, 0, h->lay.axis);
+  const uint8_t *cut = atc<uint8_t>(h, 0, h->lay.cut);
+  const float *leaf = atc<float>(h, 0, h->lay.leaf);
+  PredGroup *prog = atc<PredGroup>(h, 0, h->lay.prog);
+  const size_t cb = h->lay.chain_bytes;
+  k_pred_program<<<dim3(ngroups, h->nchain), 64 * kPredTrees, 0, h->stream>>>(
+      axis, cut, leaf, prog, m, p, D, h->H, cb);
+  constexpr int64_t kWaveLds = kPredTrees * kPredTab * sizeof(float);
+  const int64_t want = 8 * (int64_t)h->cus;
+  const int64_t words = (nt + 255) / 256;
+  if ((words + 1) / 2 * h->nchain >= want) {
+    const int64_t tiles = (words + 1) / 2;
+    k_pred_eval<2, ACC><<<dim3(grid_for(tiles, 4), h->nchain), 256, 4 * kWaveLds, h->stream>>>(
+        Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups, D, h->H, offset, cb, 1, out, sum, sumsq);
+    return;
+  }
+  int split = 1;
+  while (split < 16 && 2 * split <= ngroups && words * h->nchain * split < want) split *= 2;
+  const int nw = split > 1 ? split : 4;
+  k_pred_eval<1, ACC><<<dim3(grid_for(words, split > 1 ? 1 : 4), h->nchain), 64 * nw,
+                        nw * kWaveLds, h->stream>>>(Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups,
+                                                    D, h->H, offset, cb, split, out, sum, sumsq);
+}
+
 }  // namespace
 
 extern "C" {
@@ -643,6 +603,7 @@ int bart_init(const bart_config *cfg, const uint8_t *X_b, const float *y_c, cons
   h->X = X_b;
   h->stream = (hipStream_t)stream;
   h->device = device;
+  h->cus = prop.multiProcessorCount;
   h->H = 1 << (cfg->max_depth - 1);
   h->p_nz = (int)nzl.size();
   h->V = cpt;
@@ -759,10 +720,7 @@ int bart_predict(bart_handle *h, const uint8_t *Xt, int64_t xt_stride, int64_t n
   if (!Xt || !out) return fail(BART_EINVAL, "NULL pointer argument");
   if (xt_stride < n_t || xt_stride % 16) return fail(BART_EINVAL, "xt_stride must be >= n_t and a multiple of 16");
   HIP_TRY(hipSetDevice(h->device));
-  k_predict<false><<<dim3(grid_for(n_t, kPredBlock), h->nchain), kPredBlock, 0, h->stream>>>(
-      Xt, xt_stride, n_t, h->cfg.p, atc<uint16_t>(h, 0, h->lay.axis),
-      atc<uint8_t>(h, 0, h->lay.cut), atc<float>(h, 0, h->lay.leaf), h->cfg.ntree,
-      h->cfg.max_depth, h->H, offset, h->lay.chain_bytes, out, nullptr, nullptr);
+  launch_predict<false>(h, Xt, xt_stride, n_t, offset, out, nullptr, nullptr);
   HIP_TRY(hipGetLastError());
   return BART_OK;
 }
@@ -776,10 +734,7 @@ int bart_predict_accumulate(bart_handle *h, const uint8_t *Xt, int64_t xt_stride
   if (xt_stride < n_t || xt_stride % 16) return fail(BART_EINVAL, "xt_stride must be >= n_t and a multiple of 16");
   if (n_t > ((int64_t)1 << 40)) return fail(BART_ENOTSUP, "n_t too large");
   HIP_TRY(hipSetDevice(h->device));
-  k_predict<true><<<dim3(grid_for(n_t, kPredBlock), h->nchain), kPredBlock, 0, h->stream>>>(
-      Xt, xt_stride, n_t, h->cfg.p, atc<uint16_t>(h, 0, h->lay.axis),
-      atc<uint8_t>(h, 0, h->lay.cut), atc<float>(h, 0, h->lay.leaf), h->cfg.ntree,
-      h->cfg.max_depth, h->H, offset, h->lay.chain_bytes, nullptr, sum, sumsq);
+  launch_predict<true>(h, Xt, xt_stride, n_t, offset, nullptr, sum, sumsq);
   HIP_TRY(hipGetLastError());
   return BART_OK;
 }

@@ -1,0 +1,432 @@
+// predict.hpp -- sum-of-trees prediction f(x) = offset + sum_j g(x; T_j, M_j)
+// (eq. bartdef) at many points, on gfx950.
+//
+// Algorithm 1 follows every point through every level of every tree, which
+// costs a table read and a byte gather per level and point.  Here the trees
+// are compiled first, once per call (k_pred_program): the reachable internal
+// nodes of a tree in heap order, and the leaf value of every combination of
+// their decisions.  A point's leaf value is then a table read at the number
+// whose bits are the decisions "x >= cut", and because the nodes are the same
+// for all lanes, a decision for 4 points costs one coalesced word of the
+// node's predictor row, and a compare and an add-with-carry per point (the
+// visited nodes' decisions are those of Algorithm 1; the others do not change
+// the table's value).
+#pragma once
+#include "common.hpp"
+
+namespace bart {
+
+constexpr int kPredTrees = 16;      // trees per group of the compiled program
+constexpr int kPredTabNodes = 6;    // most internal nodes of a tree with a decision table
+constexpr int kPredTab = 1 << kPredTabNodes;
+constexpr int kPredListNodes = 31;  // most internal nodes of a tree with a leaf bit mask
+constexpr int kPredBatch = 8;       // nodes whose predictor words are in flight together
+constexpr uint32_t kPredNop = 256u << 16;  // a decision no byte takes
+
+// One group of the program.
+struct alignas(16) PredGroup {
+  uint32_t nbatch;    // batches of kPredBatch nodes, at least 1
+  uint32_t nspecial;  // trees without a decision table
+  uint32_t pad[14];
+  // trees of up to kPredTabNodes nodes (a tree without a node gets one that
+  // decides nothing): axis, cut << 16 (9 bits), bit 25 the tree's last node,
+  // its place in the group << 26
+  uint32_t node[kPredTrees * kPredTabNodes];
+  // other trees: place in the group, nodes << 8 (0: Algorithm 1)
+  uint32_t special[kPredTrees];
+  // trees of up to kPredListNodes nodes: axis | cut << 16, and the leaves of
+  // the left subtree (bit k: k-th leaf from the left)
+  uint32_t list[kPredTrees][2 * kPredListNodes];
+  // leaf value by decisions (the first node's the highest bit), or by leaf
+  // from the left
+  float tab[kPredTrees][kPredTab];
+};
+
+// The program of one chain (blockIdx.y), a group per block and a tree per
+// wave: lane l holds heap slots l and l + 64.
+__global__ void __launch_bounds__(64 * kPredTrees)
+    k_pred_program(const uint16_t *axis0, const uint8_t *cut0, const float *leaf0, PredGroup *prog0,
+                   int m, int p, int D, int H, size_t chain_bytes) {
+  __shared__ int s_nodes[kPredTrees], s_special[kPredTrees];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const size_t cb = blockIdx.y * chain_bytes;
+  const int j = blockIdx.x * kPredTrees + w;
+  const bool live = j < m;
+  const int64_t row = (int64_t)(live ? j : 0);
+  const uint16_t *ax = (const uint16_t *)((const char *)axis0 + cb) + row * H;
+  const uint8_t *ct = cut0 + cb + row * H;
+  const float *lf = (const float *)((const char *)leaf0 + cb) + row * 2 * H;
+  PredGroup &P = ((PredGroup *)((char *)prog0 + cb))[blockIdx.x];
+
+  int c[2], a[2];
+  uint64_t im[2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int h = l + 64 * r;
+    const bool in = live && h >= 1 && h < H;
+    c[r] = in ? ct[h] : 0;
+    a[r] = in ? ax[h] : 0;
+    if (a[r] >= p) a[r] = 0;
+  }
+  // internal nodes: a cut at the node and at each of its ancestors
+  {
+    const uint64_t raw[2] = {__ballot(c[0] != 0), __ballot(c[1] != 0)};
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      bool ok = c[r] != 0;
+#pragma unroll
+      for (int s = 1; s < 7; ++s) {
+        const int q = (l + 64 * r) >> s;
+        ok = ok && (q == 0 || ((raw[q >> 6] >> (q & 63)) & 1ull));
+      }
+      im[r] = __ballot(ok);
+    }
+  }
+  const int n = __popcll(im[0]) + __popcll(im[1]);
+  auto inner = [&](int h) { return h < H && (((h < 64 ? im[0] : im[1]) >> (h & 63)) & 1ull); };
+  auto below = [](const uint64_t (&b)[2], int k) {  // bits of b below bit k < 128
+    return k < 64 ? __popcll(b[0] & ((1ull << k) - 1ull))
+                  : __popcll(b[0]) + __popcll(b[1] & ((1ull << (k - 64)) - 1ull));
+  };
+  const bool table = n <= kPredTabNodes;
+  if (l == 0) {
+    s_nodes[w] = live && table ? (n > 0 ? n : 1) : 0;
+    s_special[w] = live && !table;
+  }
+  __syncthreads();
+  int first = 0, total = 0, sfirst = 0, stotal = 0;
+  for (int q = 0; q < kPredTrees; ++q) {
+    if (q == w) first = total, sfirst = stotal;
+    total += s_nodes[q];
+    stotal += s_special[q];
+  }
+  const int nbatch = total > 0 ? (total + kPredBatch - 1) / kPredBatch : 1;
+  if (threadIdx.x == 0) {
+    P.nbatch = (uint32_t)nbatch;
+    P.nspecial = (uint32_t)stotal;
+  }
+  if (w == 0 && total + l < nbatch * kPredBatch) P.node[total + l] = kPredNop;
+  if (!live) return;
+  if (table) {
+    const uint32_t tag = (uint32_t)w << 26;
+    if (n == 0 && l == 0) P.node[first] = kPredNop | 1u << 25 | tag;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      if ((im[r] >> l) & 1ull) {
+        const int k = below(im, l + 64 * r);
+        P.node[first + k] = (uint32_t)a[r] | (uint32_t)c[r] << 16 | (k == n - 1 ? 1u << 25 : 0u) | tag;
+      }
+    // lane l: the leaf that decisions l reach
+    int h = 1;
+    for (int lvl = 1; lvl < D; ++lvl)
+      if (inner(h)) h = 2 * h + ((l >> (n - 1 - below(im, h))) & 1);
+    if (l < 1 << n) P.tab[w][l] = lf[h];
+    return;
+  }
+  if (l == 0)
+    P.special[sfirst] = (uint32_t)w | (n <= kPredListNodes ? (uint32_t)n << 8 : 0u);
+  if (n > kPredListNodes) return;
+  // leaves from the left: bottom position k (of H) starts a leaf if the leaf
+  // above it begins there
+  uint64_t start[2];
+  int leaf_of[2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int k = l + 64 * r;
+    int h = 1, d = 0;
+    for (int lvl = 1; lvl < D; ++lvl)
+      if (inner(h)) {
+        h = 2 * h + ((k >> (D - 2 - d)) & 1);
+        ++d;
+      }
+    leaf_of[r] = h;
+    start[r] = __ballot(k < H && (k & ((1 << (D - 1 - d)) - 1)) == 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int h = l + 64 * r;
+    if ((start[r] >> l) & 1ull) P.tab[w][below(start, h)] = lf[leaf_of[r]];
+    if ((im[r] >> l) & 1ull) {
+      const int d = 31 - __clz(h), half = 1 << (D - 2 - d);
+      const int pos = (h << (D - 1 - d)) - H;  // its first bottom position; pos + half < H
+      const uint32_t left = (1u << below(start, pos + half)) - (1u << below(start, pos));
+      const int k = below(im, h);
+      P.list[w][2 * k] = (uint32_t)a[r] | (uint32_t)c[r] << 16;
+      P.list[w][2 * k + 1] = left;
+    }
+  }
+}
+
+// One decision of 4 points: code = 2 code + (byte >= cut) each, as a byte
+// compare and an add with carry (from C++ a third instruction selects 0 or 1
+// first).  The compares come together: a lane mask written by a vector
+// instruction may be read by one three instructions later at the earliest.
+__device__ __forceinline__ void pred_decide4(uint32_t (&code)[4], uint32_t x, uint32_t cut) {
+  uint64_t m0, m1, m2, m3;
+  asm("v_cmp_ge_u32_sdwa %4, %8, %9 src0_sel:BYTE_0 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %5, %8, %9 src0_sel:BYTE_1 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %6, %8, %9 src0_sel:BYTE_2 src1_sel:DWORD\n\t"
+      "v_cmp_ge_u32_sdwa %7, %8, %9 src0_sel:BYTE_3 src1_sel:DWORD\n\t"
+      "v_addc_co_u32_e64 %0, %4, %0, %0, %4\n\t"
+      "v_addc_co_u32_e64 %1, %5, %1, %1, %5\n\t"
+      "v_addc_co_u32_e64 %2, %6, %2, %2, %6\n\t"
+      "v_addc_co_u32_e64 %3, %7, %3, %3, %7"
+      : "+v"(code[0]), "+v"(code[1]), "+v"(code[2]), "+v"(code[3]), "=&s"(m0), "=&s"(m1),
+        "=&s"(m2), "=&s"(m3)
+      : "v"(x), "s"(cut));
+}
+
+// The compiled trees at a tile of 64 x 4 W points per wave: word u of lane l
+// holds the 4 points at 4 (64 (W tile + u) + l).  split = 1: every wave has a
+// tile of its own.  Else the waves of a block share one tile and the groups
+// of trees, in order, among them, and their fp64 sums are added in that
+// order.  blockIdx.y = chain.  ACC: add f and f^2 (fp64) to sum and sumsq
+// instead of writing fp32(f) to out.
+typedef uint32_t u32_any __attribute__((aligned(1)));  // Xt has no alignment of its own
+template <class T>
+using cptr = const __attribute__((address_space(4))) T *;  // scalar loads
+
+template <int W, bool ACC>
+__global__ void __launch_bounds__(1024)
+    k_pred_eval(const uint8_t *Xt, int64_t ldx, int64_t nt, int p, const PredGroup *prog0,
+                const uint16_t *axis0, const uint8_t *cut0, const float *leaf0, int ngroups, int D,
+                int H, double offset, size_t chain_bytes, int split, float *out0, double *sum0,
+                double *sumsq0) {
+  extern __shared__ __align__(16) char s_raw[];
+  constexpr size_t kWaveLds = kPredTrees * kPredTab * sizeof(float);  // also 64 x 4 W fp64
+  static_assert(kWaveLds >= 64 * 4 * W * sizeof(double), "the partial sums reuse the tables");
+  const int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nw = (int)blockDim.x >> 6;
+  float *const tab = (float *)(s_raw + w * kWaveLds);
+  const size_t cb = blockIdx.y * chain_bytes;
+  const char *prog = (const char *)prog0 + cb;
+  const int64_t tiles = (nt + 256 * W - 1) / (256 * W);
+  const int64_t step = (int64_t)gridDim.x * (split > 1 ? 1 : nw);
+  const int g0 = split > 1 ? (int)((int64_t)ngroups * w / split) : 0;
+  const int g1 = split > 1 ? (int)((int64_t)ngroups * (w + 1) / split) : ngroups;
+
+  for (int64_t tile = split > 1 ? blockIdx.x : (int64_t)blockIdx.x * nw + w; tile < tiles;
+       tile += step) {
+    // byte offset of this lane's words in a predictor row (the first word
+    // stands in past the last point)
+    int64_t at[W];
+    uint32_t vo[W];
+    const int64_t base = 256 * (int64_t)W * tile;
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      at[u] = base + 256 * u + 4 * l;
+      vo[u] = at[u] < nt ? (uint32_t)(256 * u + 4 * l) : 0u;
+    }
+    const uint8_t *X = Xt + base;
+    double acc[W][4];
+    float pend[W][4];  // leaf values read but not yet added
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[u][b] = 0.0, pend[u][b] = 0.f;
+
+    struct Batch {
+      uint32_t node[kPredBatch];
+      uint32_t x[kPredBatch][W];
+    };
+    auto group = [&](int g) {
+      return (cptr<PredGroup>)(prog + (size_t)g * sizeof(PredGroup));
+    };
+    auto fetch = [&](int g, int b, Batch &B) {
+      const cptr<PredGroup> G = group(g);
+#pragma unroll
+      for (int e = 0; e < kPredBatch; ++e) B.node[e] = G->node[b * kPredBatch + e];
+#pragma unroll
+      for (int e = 0; e < kPredBatch; ++e) {
+        // (32-bit lane offsets from a uniform row, kept that way)
+#pragma unroll
+        for (int u = 0; u < W; ++u) asm volatile("" : "+v"(vo[u]));
+        const gptr<const uint8_t> xr = gbl(X) + (int64_t)(B.node[e] & 0xffffu) * ldx;
+#pragma unroll
+        for (int u = 0; u < W; ++u) B.x[e][u] = *(gptr<const u32_any>)(xr + vo[u]);
+      }
+    };
+    uint32_t code[W][4];
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) code[u][b] = 0;
+    auto process = [&](const Batch &B) {
+#pragma unroll
+      for (int e = 0; e < kPredBatch; ++e) {
+        const uint32_t node = B.node[e];
+        const uint32_t cut = (node >> 16) & 0x1ffu;
+#pragma unroll
+        for (int u = 0; u < W; ++u) pred_decide4(code[u], B.x[e][u], cut);
+        if ((node >> 25) & 1u) {  // uniform
+          const float *tt = tab + (node >> 26) * kPredTab;
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+              acc[u][b] += (double)pend[u][b];
+              pend[u][b] = tt[code[u][b]];
+              code[u][b] = 0;
+            }
+        }
+      }
+    };
+    // trees of more nodes
+    auto special = [&](int g) {
+      const cptr<PredGroup> G = group(g);
+      const int ns = (int)G->nspecial;
+      for (int q = 0; q < ns; ++q) {
+        const uint32_t tag = G->special[q];
+        const int tr = (int)(tag & 0xffu), n = (int)(tag >> 8);
+        if (n > 0) {
+          // every node clears the leaves of its left subtree for a point that
+          // goes right; the leaf is the leftmost one left
+          uint32_t v[W][4];
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[u][b] = ~0u;
+          for (int k = 0; k < n; ++k) {
+            const uint32_t node = G->list[tr][2 * k], left = G->list[tr][2 * k + 1];
+            const gptr<const uint8_t> xr = gbl(X) + (int64_t)(node & 0xffffu) * ldx;
+            const uint32_t cut = node >> 16, keep = ~left;
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+              const uint32_t x = *(gptr<const u32_any>)(xr + vo[u]);
+#pragma unroll
+              for (int b = 0; b < 4; ++b)
+                v[u][b] &= ((x >> (8 * b)) & 0xffu) >= cut ? keep : ~0u;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              acc[u][b] += (double)tab[tr * kPredTab + (__ffs((int)v[u][b]) - 1)];
+        } else {
+          // Algorithm 1
+          const int64_t j = (int64_t)g * kPredTrees + tr;
+          const gptr<const uint16_t> ax = gbl((const uint16_t *)((const char *)axis0 + cb)) + j * H;
+          const gptr<const uint8_t> ct = gbl(cut0 + cb) + j * H;
+          const gptr<const float> lf = gbl((const float *)((const char *)leaf0 + cb)) + j * 2 * H;
+          int h[W][4];
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) h[u][b] = 1;
+          for (int lvl = 1; lvl < D; ++lvl)
+#pragma unroll
+            for (int u = 0; u < W; ++u)
+#pragma unroll
+              for (int b = 0; b < 4; ++b) {
+                const int q = h[u][b] < H ? h[u][b] : 0;
+                const int cv = q ? ct[q] : 0;
+                const int a = ax[q] < p ? ax[q] : 0;
+                const bool in = at[u] + b < nt;
+                const int xv = cv && in ? gbl(X)[(int64_t)a * ldx + vo[u] + b] : 0;
+                if (cv) h[u][b] = 2 * h[u][b] + (xv >= cv ? 1 : 0);
+              }
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[u][b] += (double)lf[h[u][b]];
+        }
+      }
+    };
+
+    if (g0 < g1) {
+      // the stream of batches of all groups, the next one always in flight;
+      // the tables of a group are read ahead likewise and stored to LDS when
+      // the group begins (this wave's own copy: no barrier)
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      constexpr int kQuads = kPredTrees * kPredTab / 256;
+      u32x4 tq[kQuads];
+      auto fetch_tab = [&](int g) {
+        const gptr<const u32x4> q =
+            gbl((const u32x4 *)(prog + (size_t)g * sizeof(PredGroup) + offsetof(PredGroup, tab)));
+#pragma unroll
+        for (int k = 0; k < kQuads; ++k) tq[k] = q[64 * k + l];
+      };
+      auto store_tab = [&]() {
+#pragma unroll
+        for (int k = 0; k < kQuads; ++k) ((u32x4 *)tab)[64 * k + l] = tq[k];
+      };
+      int g = g0, b = 0, nb = (int)group(g)->nbatch;
+      fetch_tab(g);
+      Batch B0, B1;
+      fetch(g, 0, B0);
+      store_tab();
+      if (g + 1 < g1) fetch_tab(g + 1);
+      // the batch after (g, b): in this group, or the first of the next (the
+      // same one again where there is none)
+      auto fetch_next = [&](Batch &B) {
+        const bool here = b + 1 < nb;
+        const int gn = here || g + 1 >= g1 ? g : g + 1;
+        fetch(gn, here ? b + 1 : 0, B);
+      };
+      // past a batch; at the end of a group its other trees, then the tables
+      // of the next; false at the end
+      auto advance = [&]() -> bool {
+        if (++b < nb) return true;
+#pragma unroll
+        for (int u = 0; u < W; ++u)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            acc[u][q] += (double)pend[u][q];
+            pend[u][q] = 0.f;
+          }
+        special(g);
+        if (++g >= g1) return false;
+        store_tab();
+        if (g + 1 < g1) fetch_tab(g + 1);
+        b = 0;
+        nb = (int)group(g)->nbatch;
+        return true;
+      };
+      for (;;) {
+        fetch_next(B1);
+        process(B0);
+        if (!advance()) break;
+        fetch_next(B0);
+        process(B1);
+        if (!advance()) break;
+      }
+    }
+
+    auto emit = [&](int64_t i, double s) {
+      const int64_t o = blockIdx.y * nt + i;
+      const double f = offset + s;
+      if (ACC) {
+        sum0[o] += f;
+        sumsq0[o] += f * f;
+      } else {
+        out0[o] = (float)f;
+      }
+    };
+    if (split > 1) {
+      double *const part = (double *)tab;  // [W][4][64] of this wave
+#pragma unroll
+      for (int u = 0; u < W; ++u)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) part[(u * 4 + b) * 64 + l] = acc[u][b];
+      __syncthreads();
+      for (int q = threadIdx.x; q < 256 * W; q += blockDim.x) {
+        // point q of the tile: lane (q / 4) mod 64 of word q / 256
+        const int k = ((q >> 8) * 4 + (q & 3)) * 64 + ((q >> 2) & 63);
+        double s = 0.0;
+        for (int v = 0; v < split; ++v) s += ((const double *)(s_raw + v * kWaveLds))[k];
+        if (base + q < nt) emit(base + q, s);
+      }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int u = 0; u < W; ++u)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (at[u] + b < nt) emit(at[u] + b, acc[u][b]);
+    }
+  }
+}
+
+}  // namespace bart
