@@ -33,7 +33,10 @@ __device__ __forceinline__ gptr<T> gbl(T *p) {
 struct Prop {
   int32_t move, eta, axis, cut;
   int32_t nG, nP, L, rank_l;  // #G(T), #P(T), leaves of the larger tree, rank of 2*eta
-  int32_t rank_r, pad0, pad1, pad2;
+  int32_t rank_r;
+  uint32_t head0;             // move | L << 8 | rank_l << 16 | eta << 24 (rank_l 0 without a move)
+  uint32_t head1;             // cut | axis << 16
+  int32_t pad;
   uint64_t mask[4];           // bit h set iff heap slot h is a leaf of the larger tree
   double c_prior;             // log r minus the marginal-likelihood term
   double ln_u;                // log of the accept uniform

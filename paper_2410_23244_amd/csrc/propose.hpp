@@ -364,7 +364,10 @@ __device__ __noinline__ void propose_tree(const SweepArgs *__restrict__ A, Key k
     P.L = L;
     P.rank_l = rank_l;
     P.rank_r = rank_r;
-    P.pad0 = P.pad1 = P.pad2 = 0;
+    P.head0 = (uint32_t)move | (uint32_t)L << 8 | (uint32_t)(move != kNone ? rank_l : 0) << 16 |
+              (uint32_t)eta << 24;
+    P.head1 = (uint32_t)cut | (uint32_t)a << 16;
+    P.pad = 0;
     for (int k = 0; k < 4; ++k) P.mask[k] = big[k];
     P.c_prior = c_prior;
     P.ln_u = ln_u;

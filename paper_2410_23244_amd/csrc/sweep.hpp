@@ -10,28 +10,36 @@
 // (predictor-major u8, coalesced 4-byte chunks).
 //
 // There is no coordinating workgroup.  Per tree step j, every workgroup
-//   1. has its per-leaf partial residual sums of tree j (and, for a GROW,
-//      the count of its points going right) in its own mailbox, as 64-bit
-//      words carrying a 20-bit step number over a 44-bit payload, so a
+//   1. has its per-leaf partial residual sums of tree j (and the count of its
+//      points that a GROW of tree j+1 sends right) in its own mailbox, as
+//      64-bit words carrying a 20-bit step number over a 44-bit payload, so a
 //      reader needs no fence and no separate flag (posted by the waves that
-//      formed them at the end of the previous step; the streamed kernel
-//      posts them at the start of the step);
-//   2. routes its points through tree j+1 (the route depends only on the
+//      formed them at the end of the previous step);
+//   2. routes its points through tree j+2 (the route depends only on the
 //      index cache and the proposal, sec. 3.3 "Computations parallel across
 //      trees") while the other mailboxes fill;
 //   3. reads all mailboxes in one fixed order and sums them in fp64, so every
-//      workgroup holds bit-identical totals; from them it computes the MH
-//      decision (item 9) and the leaf draws (item 10) itself: the same code
-//      on the same inputs gives the same result everywhere;
+//      workgroup holds bit-identical totals; from them every wave takes the
+//      MH decision (item 9) and the leaf draws (item 10) itself: the same
+//      code on the same inputs gives the same result everywhere;
 //   4. applies r += old - new to its residuals and rewrites its part of the
 //      index row where the tree changed (item 11);
 //   5. accumulates tree j+1's partial sums from the updated residuals in
 //      per-lane private LDS bins and reduces them in a fixed order; the wave
-//      that forms a total posts it (item 1 of step j+1).
-// One cross-workgroup hop per tree.  Tree j's structure, leaf values and
-// counts are written by its owner workgroup (j mod G) and read by all in
-// the next sweep; the sigma^2 step publishes them with release/acquire
-// fences.
+//      that forms a total posts it (item 1 of step j+1).  Beside the totals,
+//      other waves make what tree j+1's decision needs besides its sums from
+//      the counts.
+// One cross-workgroup hop and two workgroup barriers per tree (the streamed
+// kernel routes tree j+1 and takes its right-count with its sums; its
+// decision is made by some waves and handed to the others over a third
+// barrier).  Tree j's structure, leaf values and counts are written by its
+// owner workgroup (j mod G) and read by all in the next sweep; the sigma^2
+// step publishes them with release/acquire fences.
+// What bounds a step at these sizes is neither bandwidth nor the exchange's
+// load latency alone but the instructions a wave runs one after the other:
+// about 1,000 per wave and tree step at n = 1e6, 2 waves per SIMD, I-cache
+// misses none, half of the wave cycles waiting.  So work is taken out of the
+// waves' common path, or done for 4 points in one word.
 #pragma once
 #include "common.hpp"
 #include "propose.hpp"
@@ -51,7 +59,7 @@ constexpr uint32_t kSpinLimit = 1u << 21;
 // last thread of the workgroup (a polling thread) stamps the end of its
 // reduce, the start and end of its route, its loads, and the start and the
 // end of its polls.  The ordinary build compiles none of it.
-constexpr int kClockStart = 205, kClockSteps = 48, kClockPh = 20;
+constexpr int kClockStart = 205, kClockSteps = 32, kClockPh = 20;
 #ifdef BART_PHASE_CLOCKS
 __device__ uint64_t g_phase_clock[kMaxGrid][kClockSteps][kClockPh];
 __shared__ uint64_t clk_lds[kClockSteps][kClockPh];
@@ -90,7 +98,10 @@ __device__ __forceinline__ constexpr int clock_slot(int) { return -1; }
 #endif
 constexpr int kNullRank = kMaxLeaves;  // rank of a padding point (slot 0): no bin, zero delta
 constexpr int kBadRank = 255;          // rank of any other non-leaf slot: likewise, and flagged
-constexpr int kRing = 4;  // proposal contexts in flight: decide j, route j+1, rows j+2, load j+3
+// proposal contexts: the streamed kernel has j (decide) to j+3 (load) in
+// flight, the register kernel j to j+4
+constexpr int kRing = 8;
+constexpr int kNodeRing = 4;  // tree snapshots of the streamed kernel
 // Ranks per pass of the streamed kernel's LDS bins, one bin per lane and chunk
 // position (16).
 constexpr int kSlotRanks = kBinFloats / (4 * kBlock);
@@ -210,13 +221,13 @@ struct Ctx {
   Prop pr;
   uint8_t rank_of[256];   // heap slot -> rank among larger-tree leaves (kNullRank: slot 0,
                           // kBadRank: another non-leaf)
-  uint16_t heap_of[256];  // rank -> heap slot; 0 from kNullRank on
-  uint16_t ax[kMaxLeaves];       // without an index cache: the tree's axis and cut per
-  uint8_t ct[kMaxLeaves];        // internal heap slot, for Algorithm 1
+  uint8_t heap_of[256];   // rank -> heap slot; 0 from kNullRank on
 };
 
-// Without an index cache: the internal nodes of a tree snapshot, by ring slot.
+// Without an index cache: a tree snapshot and its internal nodes, by ring slot.
 struct NodeList {
+  uint16_t ax[kMaxLeaves];   // axis and cut per internal heap slot, for Algorithm 1
+  uint8_t ct[kMaxLeaves];
   uint64_t imask;            // internal heap slots below 64
   uint16_t axis8[8];         // axis and cut of the first 8 internal nodes
   uint8_t cut8[8];
@@ -238,34 +249,60 @@ struct TreeData {
   double eta_z;
 };
 
+// Register kernel: everything tree j's decision needs besides its sums, from
+// counts, stored values and normals alone (sec. 3.3 items 4, 5, 8), computed
+// by one wave a step ahead.  Per rank of the larger tree with count n, old
+// value mu and normal z: S = R + lnm with lnm = n mu; the draw S la + lb with
+// e = sigma^2 + n sigma_mu^2, la = sigma_mu^2 / e, lb = mu_mu sigma^2 / e + z
+// sqrt(sigma^2 sigma_mu^2 / e).
+struct TreeConst {
+  double la[kMaxLeaves], lb[kMaxLeaves], lnm[kMaxLeaves];
+  float mu[kMaxLeaves];
+  int32_t n[kMaxLeaves];
+  // the move's merged leaf (its draw (Sl + Sr) u[0] + u[1]), n mu_mu of the
+  // left, right and merged leaf (u[2..4]), the bound u[5] that the residual
+  // part of the likelihood ratio is compared with, the ratio's other part u[6]
+  // (for the trace), and u[7] = 1 / (2 sigma^2)
+  double u[8];
+};
+
 struct Shared {
+  // its residual delta per rank: old value - new value; 0 from kNullRank on
+  // (first: an LDS instruction's offset reaches it)
+  float dlt[256];
   alignas(16) float bins[kBinFloats];
   Ctx ctx[kRing];
-  TreeData td[2];
+  union {
+    TreeConst tc[2];  // register kernel, by tree parity
+    struct {          // streamed kernel
+      TreeData td[2];
+      // constants of tree j's decision that do not depend on its sums,
+      // computed while the mailboxes fill: per rank of a leaf whose count is
+      // known, the new value is S la + lb and S = R + lnm; the merged leaf
+      // likewise (ma, mb); for a PRUNE, the count-only parts of the likelihood
+      // ratio
+      double la[kMaxLeaves], lb[kMaxLeaves], lnm[kMaxLeaves];
+      double ma, mb, pdet, pdL, pdR, pdP, gs2eP, lgs2eP;
+    };
+  };
   double part[kBlock];
   double tot[kMaxLeaves + 1];
   double S[kMaxLeaves];
   double cntd[kMaxLeaves];
   float newv[kMaxLeaves];      // new value of each larger-tree leaf if it stays a leaf
-  float dlt[256];              // its residual delta: old value - new value; 0 from kNullRank on
   float newv_m;                // new value of eta if the move ends merged
   double wave_part[kWaves];
-  uint64_t solo[kMaxLeaves + 1];  // one workgroup per chain: its own mailbox words
+  uint64_t solo[kMaxLeaves + 2];  // one workgroup per chain: its own mailbox words
   double sigma2;
+  double sd_unit;    // sigma sigma_mu
   double sig_gamma;  // Gamma((nu+n)/2, 1) variate of the next sigma^2 draw
   double dec_logr;
-  // constants of tree j's decision that do not depend on its sums, computed
-  // while the mailboxes fill: per rank of a leaf whose count is known, the new
-  // value is S la + lb and S = R + lnm; the merged leaf likewise (ma, mb);
-  // for a PRUNE, the count-only parts of the likelihood ratio
-  double la[kMaxLeaves], lb[kMaxLeaves], lnm[kMaxLeaves];
-  double ma, mb, pdet, pdL, pdR, pdP, gs2eP, lgs2eP;
   uint64_t stats[6];  // workgroup 0: move statistics of this launch
-  int nr[2];  // GROW right-counts of the trees being routed, by tree parity
+  int nr[4];  // GROW right-counts of the trees being routed, by tree mod 4 (streamed: mod 2)
   int flags;  // bit0 accept, bit1 merged
   int abort_flag;
   int dev_err;
-  NodeList nl[kRing];  // last, so the other members keep their offsets
+  NodeList nl[kNodeRing];  // last, so the other members keep their offsets
 };
 
 template <int IB>
@@ -305,8 +342,10 @@ __device__ __forceinline__ void build_rank_slot(const SweepArgs *__restrict__ A,
     k += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mw >> 32),
                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mw, 0u));
     r = (uint8_t)k;
-    c.heap_of[k] = (uint16_t)h;
+    c.heap_of[k] = (uint8_t)h;
   }
+  // the node a GROW splits, a leaf until then: the left child's rank
+  if (c.pr.move == kGrow && h == c.pr.eta) r = (uint8_t)c.pr.rank_l;
   c.rank_of[h] = r;
 }
 
@@ -319,23 +358,22 @@ __device__ __forceinline__ void build_ranks(const SweepArgs *__restrict__ A, Ctx
 // nonzero; a slot outside the tree has cut 0), numbered in heap order by a
 // ballot per 64 slots.  Wave 4 (it holds no rank slot), after the snapshot
 // is in LDS.
-__device__ __forceinline__ void build_inodes(const SweepArgs *__restrict__ A, const Ctx &c,
-                                             NodeList &nl) {
+__device__ __forceinline__ void build_inodes(const SweepArgs *__restrict__ A, NodeList &nl) {
   const int t = (int)threadIdx.x, lane = t & 63;
   if ((t >> 6) != 4) return;
   const int H = A->H;
   int base = 0;
   for (int h0 = 0; h0 < H; h0 += 64) {
     const int h = h0 + lane;
-    const bool in = h >= 1 && h < H && c.ct[h] != 0;
+    const bool in = h >= 1 && h < H && nl.ct[h] != 0;
     const uint64_t bal = __ballot(in);
     const int k = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
     if (h < H) nl.nidx[h] = in ? (uint8_t)k : (uint8_t)kNoNode;
     if (in) nl.nh[k] = (uint8_t)h;
     if (in && k < 8) {
-      nl.axis8[k] = c.ax[h];
-      nl.cut8[k] = c.ct[h];
+      nl.axis8[k] = nl.ax[h];
+      nl.cut8[k] = nl.ct[h];
     }
     if (h0 == 0 && lane == 0) nl.imask = bal;
     base += __popcll(bal);
@@ -596,7 +634,7 @@ __device__ __noinline__ void trace_tree_step(bart_trace *R, Shared &sh, const Ct
   const int acc = sh.flags & 1, merged = (sh.flags >> 1) & 1;
   if (t < 256) {
     const int rnk = c.rank_of[t];
-    const bool in = rnk < kNullRank && t < 2 * H;  // a leaf of the larger tree
+    const bool in = rnk < kNullRank && t < 2 * H && c.heap_of[rnk] == t;  // a leaf of the larger tree
     R->count[t] = in ? (int32_t)sh.cntd[rnk] : 0;
     R->sum[t] = in ? sh.S[rnk] : 0.0;
     float lv = 0.f;
@@ -930,6 +968,7 @@ __device__ __forceinline__ void sigma2_tail(const SweepArgs *__restrict__ A, con
     // the probit model holds sigma^2 at 1 and draws latents instead
     const double s2 = A->probit ? sh.sigma2 : sigma2_of(A, ssr_all, sh.sig_gamma);
     sh.sigma2 = s2;
+    sh.sd_unit = A->sigma_mu * sqrt(s2);
     if (w == 0) {
       A->ctl->sigma2 = s2;
       A->ctl->sweep = s + 1;
@@ -963,6 +1002,386 @@ __device__ __forceinline__ void sigma2_tail(const SweepArgs *__restrict__ A, con
   __syncthreads();
 }
 
+// ------------------------------------------------------- register kernel
+// The decision of a tree step as the register kernel takes it.  All of it
+// that depends on counts alone (sec. 3.3 items 4, 5, 8) is made a step ahead
+// by one wave (decide_consts): a tree is routed two steps before its own, so
+// its GROW right-count travels with the sums of the tree before it.  What is
+// left when the sums arrive is a dozen dependent fp64 operations, and every
+// wave takes them for itself (decide_all) from the same words: no barrier
+// and no LDS round trip between the decision and the residual update.
+// (Before, the constants of a GROW's children were made after the gather and
+// the decision handed from four waves to the others through LDS and a
+// barrier.  With the route in packed bytes, per call of one sweep: n = 1e6,
+// 200 trees 1,063 -> 1,018 us, n = 1e5 959 -> 892 us; n = 1e3, 50 trees, 10
+// sweeps, where one workgroup has no gather to hide the constants behind,
+// 2,770 -> 2,083 us.)
+
+// The fields of a proposal that later steps use, as two scalars.
+struct Head {
+  uint32_t a, b;
+  __device__ int move() const { return (int)(a & 0xffu); }
+  __device__ int L() const { return (int)((a >> 8) & 0xffu); }
+  __device__ int kl() const { return (int)((a >> 16) & 0xffu); }  // the right child's is kl + 1
+  __device__ int eta() const { return (int)(a >> 24); }
+  __device__ int cut() const { return (int)(b & 0xffffu); }
+  __device__ int axis() const { return (int)(b >> 16); }
+};
+
+__device__ __forceinline__ Head scalar(const Head &h) {
+  return Head{(uint32_t)__builtin_amdgcn_readfirstlane((int)h.a),
+              (uint32_t)__builtin_amdgcn_readfirstlane((int)h.b)};
+}
+
+__device__ __forceinline__ Head read_head(const Ctx &c) {
+  return scalar(Head{c.pr.head0, c.pr.head1});
+}
+
+// x of lane l, as a scalar pair (l is wave-uniform)
+__device__ __forceinline__ double lane_f64(double x, int l) {
+  const uint64_t b = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// v plus its value in the lane 8 (16, 32) away: rows of 16 rotated by 8, odd
+// and even rows exchanged, halves exchanged
+__device__ __forceinline__ double add_xor8(double v) { return v + dpp_f64<0x128, 0xF>(v); }
+template <bool kHalves>
+__device__ __forceinline__ double add_swapped(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 l, h;
+  if (kHalves) {
+    l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  } else {
+    l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  }
+  return __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
+
+// Where the gathered words are: word k as the sum of part[r stride + k] over
+// rows r.
+struct Gathered {
+  int rows, stride;
+};
+
+__device__ __forceinline__ Gathered scalar(const Gathered &g) {
+  return Gathered{__builtin_amdgcn_readfirstlane(g.rows), __builtin_amdgcn_readfirstlane(g.stride)};
+}
+
+// Poll words 0..K-1 of every mailbox until they carry step number seq, as
+// gather_polls, for up to 64 words, all of them fp64 values (a count of at most
+// 2^33 is exact in a word's 33 significant bits).  Lane (sub, k) of a polling wave, k <
+// stride (the power of two >= K, at least 8), sums word k of a range of
+// workgroups, 8 loads in flight; the subs of a wave are then added in
+// registers, and the wave's sums are one row of sh.part.  The number of
+// polling waves, 1, 2, 4 or 8, and so the order of every sum, depends on G
+// and K only: the fewest that leave a lane at most 8 workgroups.  Ends with
+// an LDS barrier, after which abort_flag is final for this step.
+template <class SH>
+__device__ __forceinline__ Gathered gather_rows(const SweepArgs *__restrict__ A, SH &sh, int par,
+                                                uint32_t seq, int K, uint32_t limit, int wv,
+                                                int clk = -1) {
+  const int G = A->G;
+  if (G == 1) {
+    lds_barrier();  // the words were staged by the waves that formed them
+    return Gathered{0, 0};
+  }
+  if (K > 64) {
+    const int nseg = gather_polls(A, sh, par, seq, K, K, limit, clk);
+    return Gathered{nseg, K};
+  }
+#ifdef BART_PHASE_CLOCKS
+  uint32_t poll_loads = 0;
+#endif
+  const int lg = K <= 8 ? 3 : K <= 16 ? 4 : K <= 32 ? 5 : 6;
+  const int subs = 64 >> lg;  // per wave
+  int nw = 1;
+  while (nw < kWaves && 8 * nw * subs < G) nw *= 2;
+  const int span = (G + nw * subs - 1) / (nw * subs);
+  BART_CLOCK_LAST(clk, 17);
+  const int row = wv;
+  if (row < nw) {
+    const int lane = (int)threadIdx.x & 63;
+    const int k = lane & ((1 << lg) - 1);
+    const int g0 = (row * subs + (lane >> lg)) * span;
+    const int g1 = k < K ? min(G, g0 + span) : 0;
+    const uint64_t *base = A->pub + (int64_t)par * G * kStride + k;
+    double acc = 0.0;
+#pragma unroll 1
+    for (int gb = g0; gb < g1; gb += 8) {
+      uint64_t w[8];
+      uint32_t pending = (g1 - gb >= 8) ? 0xFFu : ((1u << (g1 - gb)) - 1u);
+      uint32_t spins = 0;
+      const uint64_t *pb = base + (int64_t)gb * kStride;
+      while (pending) {
+        BART_POLL_COUNT(__popc(pending));
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if ((pending >> u) & 1u) w[u] = ld_dev(pb + u * kStride);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (((pending >> u) & 1u) && seq_of(w[u]) == seq) pending &= ~(1u << u);
+        if (pending) {
+          __builtin_amdgcn_s_sleep(1);
+          if (++spins > limit) {
+            sh.abort_flag = 1;
+            break;
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (gb + u < g1) acc += unpack_f64(w[u]);
+    }
+    // lanes whose range is empty hold 0, so every lane takes part
+    if (lg <= 3) acc = add_xor8(acc);
+    if (lg <= 4) acc = add_swapped<false>(acc);
+    if (lg <= 5) acc = add_swapped<true>(acc);
+    if (lane < K) sh.part[(row << lg) + lane] = acc;
+  }
+  BART_CLOCK_LAST(clk, 18);
+#ifdef BART_PHASE_CLOCKS
+  if (clk >= 0 && poll_loads) atomicAdd((unsigned long long *)&clk_lds[clk][kClockPh - 1],
+                                        (unsigned long long)poll_loads);
+#endif
+  lds_barrier();
+  return Gathered{nw, 1 << lg};
+}
+
+// Word k < K (may vary by lane) of the gathered words.
+template <class SH>
+__device__ __forceinline__ double gathered(const SH &sh, const Gathered &g, int k) {
+  if (g.rows == 0) return unpack_f64(sh.solo[k]);  // one workgroup: its own words
+  const double *p = sh.part + k;
+  double a = p[0];
+  if (g.rows == 2) {
+    a += p[g.stride];
+  } else if (g.rows == 4) {
+    const double b = p[g.stride], c = p[2 * g.stride], d = p[3 * g.stride];
+    a = ((a + b) + c) + d;
+  } else if (g.rows == 8) {
+    double x[8];
+#pragma unroll
+    for (int r = 1; r < 8; ++r) x[r] = p[r * g.stride];
+#pragma unroll
+    for (int r = 1; r < 8; ++r) a += x[r];
+  } else {
+#pragma unroll 1
+    for (int r = 1; r < g.rows; ++r) a += p[r * g.stride];
+  }
+  return a;
+}
+
+// Stored counts, values and normals of tree j, for the wave that makes its
+// constants: rank `rank`'s in c0, and of the move's node and its children.
+struct ConstRegs {
+  int32_t cnt;
+  float mu;
+  double z;
+  int32_t eta_cnt, cl, cr;
+  float eta_mu;
+  double eta_z;
+};
+
+__device__ __forceinline__ ConstRegs load_const(const SweepArgs *__restrict__ A, const Ctx &c,
+                                                const Head &h, int j, int64_t s, int rank) {
+  const int H = A->H;
+  const int64_t row = (int64_t)j * 2 * H;
+  const gptr<const int32_t> cnt = gbl((const int32_t *)A->count) + row;
+  const gptr<const float> leaf = gbl((const float *)A->leaf) + row;
+  const gptr<const double> z = gbl((const double *)A->z) + (int64_t)(s & 1) * A->m * 2 * H + row;
+  const int slot = rank < h.L() ? c.heap_of[rank] : 1;
+  const int eta = h.move() != kNone ? h.eta() : 1;
+  ConstRegs r;
+  r.cnt = cnt[slot];
+  r.mu = leaf[slot];
+  r.z = z[slot];
+  r.eta_cnt = cnt[eta];
+  r.eta_mu = leaf[eta];
+  r.eta_z = z[eta];
+  r.cl = cnt[h.move() == kPrune ? 2 * eta : 1];
+  r.cr = cnt[h.move() == kPrune ? 2 * eta + 1 : 1];
+  return r;
+}
+
+// 1 / sqrt(x) from the hardware's estimate and two Newton steps (within two
+// ulps).
+__device__ __forceinline__ double rsq_fast(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+
+// The draw constants of tree j's decision into tc, by one wave; r0 holds
+// load_const of rank = lane, n_right the grid's count of points a GROW sends
+// right.
+__device__ __forceinline__ void draw_consts(const SweepArgs *__restrict__ A, Shared &sh,
+                                            TreeConst &tc, const Ctx &c, const Head &h, int j,
+                                            int64_t s, const ConstRegs &r0, double n_right) {
+  const int lane = (int)threadIdx.x & 63;
+  const double s2 = sh.sigma2, v2 = A->sigma_mu * A->sigma_mu, mm = A->mu_mu;
+  const double sd = sh.sd_unit;  // sqrt(s2 v2)
+  const bool grow = h.move() == kGrow;
+  // item L: the merged leaf
+  const int items = h.L() + (h.move() != kNone ? 1 : 0);
+  for (int u = lane; u < items; u += 64) {
+    const ConstRegs r = u < 64 ? r0 : load_const(A, c, h, j, s, u);
+    const bool left = grow && u == h.kl(), right = grow && u == h.kl() + 1, merged = u == h.L();
+    double n = (double)r.cnt, z = r.z;
+    float mu = r.mu;
+    if (left || right) {
+      n = right ? n_right : (double)r.eta_cnt - n_right;
+      mu = r.eta_mu;
+    }
+    if (merged) {
+      n = grow ? (double)r.eta_cnt : (double)r.cl + (double)r.cr;
+      z = r.eta_z;
+    }
+    const double ir = rsq_fast(s2 + n * v2), ie = ir * ir;
+    const double la = v2 * ie, lb = mm * s2 * ie + z * (sd * ir);
+    if (merged) {
+      tc.u[0] = la;
+      tc.u[1] = lb;
+    } else {
+      tc.la[u] = la;
+      tc.lb[u] = lb;
+      tc.lnm[u] = n * (double)mu;
+      tc.mu[u] = mu;
+      tc.n[u] = (int32_t)n;
+    }
+  }
+}
+
+// The acceptance constants of a tree's decision, by another wave, from the
+// counts n_l and n_r of the move's two leaves.  The log marginal-likelihood
+// ratio of splitting a leaf into (L, R): the partial residuals of a leaf with
+// n points, its N(mu_mu, v2) value integrated out (sec. 2.1), are N(mu_mu 1,
+// s2 I + v2 1 1^T), so LLR = 1/2 ln(s2 eP / (eL eR)) + q, q = v2 / (2 s2)
+// (tL^2/eL + tR^2/eR - tP^2/eP) with e = s2 + n v2 and t = S - n mu_mu.
+// Accept: ln u < c_prior + LLR (GROW) or c_prior - LLR (PRUNE); only q depends
+// on the sums.
+__device__ __forceinline__ void accept_consts(const SweepArgs *__restrict__ A, Shared &sh,
+                                              TreeConst &tc, const Ctx &c, const Head &h,
+                                              double nl, double nr) {
+  const double s2 = sh.sigma2, v2 = A->sigma_mu * A->sigma_mu, mm = A->mu_mu;
+  const double eL = s2 + nl * v2, eR = s2 + nr * v2, eP = s2 + (nl + nr) * v2;
+  const double det = 0.5 * log(s2 * eP * rcp_fast(eL * eR));
+  const double d = c.pr.ln_u - c.pr.c_prior;
+  if (((int)threadIdx.x & 63) == 0) {
+    tc.u[2] = nl * mm;
+    tc.u[3] = nr * mm;
+    tc.u[4] = (nl + nr) * mm;
+    tc.u[5] = h.move() == kGrow ? d - det : -d - det;
+    tc.u[6] = det;
+    tc.u[7] = 0.5 * rcp_fast(s2);
+  }
+}
+
+struct Decision {
+  int acc, merged;  // accepted; the move ends with eta a leaf
+};
+
+// Tree j's decision and leaf draws (sec. 3.3 items 8-10) from the gathered
+// sums, by every wave for itself: all waves write the same deltas, and each
+// reads its own.  The wave with keep set also leaves the new values (rank ->
+// value in the final tree) in LDS for the owner's store.
+__device__ __forceinline__ Decision decide_all(const SweepArgs *__restrict__ A, Shared &sh,
+                                               const Ctx &c, const TreeConst &tc, const Head &h,
+                                               const Gathered &g, bool keep, bool tracing) {
+  const int lane = (int)threadIdx.x & 63;
+  const int L = h.L(), kl = h.kl();
+  const int k0 = lane < L ? lane : 0;
+  double S = gathered(sh, g, k0) + tc.lnm[k0];
+  const double la0 = tc.la[k0], lb0 = tc.lb[k0];
+  const float mu0 = tc.mu[k0];
+  double u[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) u[q] = tc.u[q];
+  if (L > 64) {  // all sums into LDS, the same from every wave
+    sh.S[k0] = S;
+    for (int k = lane + 64; k < L; k += 64) sh.S[k] = gathered(sh, g, k) + tc.lnm[k];
+  }
+  Decision d{0, 0};
+  float vm = 0.f;
+  if (h.move() != kNone) {
+    double Sl, Sr, lal, lar;
+    if (L <= 64) {
+      Sl = lane_f64(S, kl), Sr = lane_f64(S, kl + 1);
+      lal = lane_f64(la0, kl), lar = lane_f64(la0, kl + 1);
+    } else {
+      Sl = sh.S[kl], Sr = sh.S[kl + 1];
+      lal = tc.la[kl], lar = tc.la[kl + 1];
+    }
+    const double ma = u[0], mb = u[1];
+    const double SP = Sl + Sr;
+    const double tL = Sl - u[2], tR = Sr - u[3], tP = SP - u[4];
+    const double q = u[7] * (tL * tL * lal + tR * tR * lar - tP * tP * ma);
+    // GROW: u[5] < q; PRUNE: q < u[5]
+    const double diff = h.move() == kGrow ? q - u[5] : u[5] - q;
+    if (tracing && keep && lane == 0) {
+      const double llr = u[6] + q;
+      sh.dec_logr = h.move() == kGrow ? c.pr.c_prior + llr : c.pr.c_prior - llr;
+    }
+    d.acc = __builtin_amdgcn_readfirstlane(diff > 0.0 ? 1 : 0);
+    d.merged = (h.move() == kGrow) != (d.acc != 0) ? 1 : 0;
+    vm = (float)(SP * ma + mb);
+  }
+  const int to_l = d.merged ? kl : -1, to_r = d.merged ? kl + 1 : -1;
+  for (int k = lane; k < L; k += 64) {
+    const bool head = k == lane;
+    const double Sk = head ? S : sh.S[k], la = head ? la0 : tc.la[k], lb = head ? lb0 : tc.lb[k];
+    const float v = k == to_l || k == to_r ? vm : (float)(Sk * la + lb);
+    sh.dlt[k] = (head ? mu0 : tc.mu[k]) - v;
+    if (keep) {
+      sh.newv[k] = v;
+      if (tracing) {
+        sh.S[k] = Sk;
+        sh.cntd[k] = (double)tc.n[k];
+      }
+    }
+  }
+  if (tracing && keep && lane == 0) {
+    if (h.move() == kNone) sh.dec_logr = 0.0;
+    sh.flags = d.acc | (d.merged << 1);
+    sh.newv_m = vm;
+  }
+  return d;
+}
+
+// After the decision of tree j: its owner workgroup (j mod G) stores the
+// final tree, its leaves' values and counts and the structure change; by the
+// wave that wrote sh.newv.
+__device__ __forceinline__ void store_tree(const SweepArgs *__restrict__ A, const Shared &sh,
+                                           const Ctx &c, const TreeConst &tc, const Head &h,
+                                           const Decision &d, int j) {
+  const int H = A->H, lane = (int)threadIdx.x & 63;
+  const int64_t row = (int64_t)j * 2 * H;
+  for (int k = lane; k < h.L(); k += 64) {
+    if (d.merged && k == h.kl() + 1) continue;  // eta is stored once
+    const bool to_eta = d.merged && k == h.kl();
+    const int f = to_eta ? h.eta() : c.heap_of[k];
+    gbl(A->leaf)[row + f] = sh.newv[k];
+    gbl(A->count)[row + f] = to_eta ? tc.n[k] + tc.n[k + 1] : tc.n[k];
+  }
+  if (lane == 0 && d.acc) {
+    const gptr<uint8_t> ct = gbl(A->cut) + (int64_t)j * H;
+    if (h.move() == kGrow) {
+      (gbl(A->axis) + (int64_t)j * H)[h.eta()] = (uint16_t)h.axis();
+      ct[h.eta()] = (uint8_t)h.cut();
+      if (2 * h.eta() < H) ct[2 * h.eta()] = 0;
+      if (2 * h.eta() + 1 < H) ct[2 * h.eta() + 1] = 0;
+    }
+    if (h.move() == kPrune) ct[h.eta()] = 0;
+  }
+}
+
 template <int V, int IB>
 __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, const Launch &Lc,
                                            Shared &sh) {
@@ -971,15 +1390,23 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   // the thread index is re-read opaquely at every step (see the loop), so
   // addresses derived from it are recomputed rather than kept in registers
   // (or spilled) across the whole loop
-  int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // One wave each stores the owner's trees, loads proposals and builds rank
+  // tables, makes the acceptance constants and the draw constants: the last
+  // four, which have the fewest totals and (but for trees of many leaves) do
+  // not poll.  They start on it behind the bin barrier, while the first waves
+  // form the totals; on the first four, behind the totals, it made the step
+  // longer (n = 1e6: 1,118 against 1,089 us a sweep).
+  constexpr int kStoreWave = 4, kPropWave = 5, kAcceptWave = 6, kConstWave = 7;
   const int w = wg_id(A);
-  const int G = A->G, H = A->H, m = A->m;
+  const int G = A->G, m = A->m;
   const uint64_t seed = Lc.seed;
   const bool tracing = Lc.trace != nullptr;
 
   float r[V][4];
-  uint32_t rk[V];   // ranks of the tree being decided, 4 x 8 bits per chunk
-  uint32_t rk2[V];  // ranks of the next tree
+  // ranks of trees j (being decided), j + 1 and j + 2, 4 x 8 bits per chunk
+  uint32_t rk[V], rk1[V], rk2[V];
   ChunkT rawc[V];
   uint32_t rawx[V];
   // chunk v of this thread exists iff t + v kBlock < lim, lim uniform over
@@ -987,6 +1414,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   // the end has no load of its own and routes to the null rank)
   const int32_t lim = A->chunks - w * V * kBlock;
   auto chunk_ok = [&](int v) { return t + v * kBlock < lim; };
+  const bool mine = 64 * wv < lim;  // this wave has points
   // bit b: observation 4 chunk + b exists (sigma^2 step and epilogue)
   auto ok4 = [&](int v) -> uint32_t {
     const int32_t rem = A->n - 4 * ((w * V + v) * kBlock + t);
@@ -1003,7 +1431,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
       r[v][2] = q[2];
       r[v][3] = q[3];
     }
-    rk[v] = rk2[v] = 0;
+    rk[v] = rk1[v] = rk2[v] = 0;
     rawc[v] = 0;
     rawx[v] = 0;
   }
@@ -1011,24 +1439,25 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   if (t == 0) {
     sh.abort_flag = 0;
     sh.dev_err = 0;
-    sh.nr[0] = sh.nr[1] = 0;
+    for (int q = 0; q < 4; ++q) sh.nr[q] = 0;
     sh.sigma2 = A->ctl->sigma2;
+    sh.sd_unit = A->sigma_mu * sqrt(A->ctl->sigma2);
   }
   // ranks from kNullRank on: zero delta, slot 0
   if (t >= kNullRank && t < 256) sh.dlt[t] = 0.f;
   for (int q = t; q < kRing * (256 - kNullRank); q += kBlock)
     sh.ctx[q / (256 - kNullRank)].heap_of[kNullRank + q % (256 - kNullRank)] = 0;
   if (t < 6) sh.stats[t] = 0;
-  int uncounted = -1;  // tree step whose move statistics workgroup 0 has yet to count
-  int clk = -1;        // phase-clock slot of the current step (diagnostic build)
+  int clk = -1;  // phase-clock slot of the current step (diagnostic build)
 
   // ---- helpers over the pipeline ----
-  // issue the index-row and predictor-row loads of tree `tree` (its proposal in ctx)
-  auto issue_rows = [&](int tree) {
-    const Ctx &c = sh.ctx[tree & (kRing - 1)];
+  auto ctx = [&](int tree) -> Ctx & { return sh.ctx[tree & (kRing - 1)]; };
+  auto tconst = [&](int tree) -> TreeConst & { return sh.tc[tree & 1]; };
+  // issue the index-row and predictor-row loads of tree `tree`
+  auto issue_rows = [&](int tree, int axis) {
     const gptr<const ChunkT> row =
         gbl((const ChunkT *)((const char *)A->idx + (int64_t)tree * A->ldi * IB));
-    const gptr<const uint32_t> xrow = gbl((const uint32_t *)(A->X + (int64_t)c.pr.axis * A->ldx));
+    const gptr<const uint32_t> xrow = gbl((const uint32_t *)(A->X + (int64_t)axis * A->ldx));
     // unconditional loads (chunk 0 stands in for a chunk past the end)
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -1039,61 +1468,60 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
     }
   };
   // route this workgroup's points through tree `tree` (rows already loaded):
-  // rank of each point's leaf in the larger tree, GROW right-count into nr
-  auto route = [&](int tree, uint32_t (&out)[V]) {
-    const Ctx &c = sh.ctx[tree & (kRing - 1)];
-    const int move = c.pr.move, eta = c.pr.eta, cutv = c.pr.cut;
-    const int grow_eta = move == kGrow ? eta : -1;
-    // leaf of every point in the larger tree, then all rank lookups at once
-    int cp[V][4];
-    int nr = 0;
-    if (grow_eta >= 0) {
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        // a chunk past the end: index 0, the null rank, for all its points
-        const ChunkT rc = chunk_ok(v) ? rawc[v] : (ChunkT)0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int ci = IC::get(rc, b);
-          const int xi = (rawx[v] >> (8 * b)) & 0xff;
-          const bool in = ci == grow_eta;
-          const int right = xi >= cutv;
-          cp[v][b] = in ? 2 * eta + right : ci;  // below 256: eta < 128
-          nr += __popcll(__ballot(in && right));  // wave-uniform
-        }
-      }
-    } else {
-      // not a GROW (a uniform branch): every point keeps its leaf, and the
-      // predictor bytes, loaded all the same, go unused
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const ChunkT rc = chunk_ok(v) ? rawc[v] : (ChunkT)0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) cp[v][b] = IC::get(rc, b);
-      }
-    }
-    int r0[V][4];
-#pragma unroll
-    for (int v = 0; v < V; ++v)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) r0[v][b] = c.rank_of[cp[v][b]];
-    // slot 0 marks a padding point (its index entry, or no load at all past
-    // the last chunk) and has the null rank, whose delta is 0 and which falls
-    // in no bin, so no per-point mask is needed; any other non-leaf slot is
-    // an inconsistent cache, rank kBadRank (no bin, zero delta), flagged
-    int worst = 0;
+  // rank of each point's leaf in the larger tree, GROW right-count into nr.
+  // The rank table gives the points of a GROW's node the left child's rank;
+  // those at or above the cut get the next one, 4 points at a time in the
+  // bytes of a word (14 instructions per 4 points instead of about 40 with a
+  // compare, a select and a ballot per point)
+  auto route = [&](int tree, const Head &h, uint32_t (&out)[V]) {
+    const Ctx &c = ctx(tree);
+    constexpr uint32_t kTop = 0x80808080u, kLow = 0x7f7f7f7fu;
+    uint32_t bad = 0;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
+      // a chunk past the end: index 0, the null rank, for all its points
+      const ChunkT rc = chunk_ok(v) ? rawc[v] : (ChunkT)0;
+      // slot 0 marks a padding point (its index entry, or no load at all past
+      // the last chunk) and has the null rank, whose delta is 0 (and its
+      // residual is 0), so no per-point mask is needed; any other non-leaf
+      // slot is an inconsistent cache, rank kBadRank (zero delta), flagged
       uint32_t pk = 0;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        worst = max(worst, r0[v][b]);
-        pk |= (uint32_t)r0[v][b] << (8 * b);
-      }
+      for (int b = 0; b < 4; ++b) pk |= (uint32_t)c.rank_of[IC::get(rc, b)] << (8 * b);
       out[v] = pk;
+      static_assert(kBadRank == 255 && kNullRank == 128, "only kBadRank has its two top bits set");
+      bad |= pk & (pk << 1);
     }
-    if (worst == kBadRank) sh.dev_err = 1;
-    if (lane == 0 && nr) atomicAdd(&sh.nr[tree & 1], nr);
+    if (h.move() == kGrow) {  // (a uniform branch; the bytes are loaded all the same)
+      const uint32_t kl4 = (uint32_t)h.kl() * 0x01010101u;
+      const uint32_t cut4 = (uint32_t)h.cut() * 0x01010101u;
+      const uint32_t cut_low = cut4 & kLow;              // cut without its top bit
+      const uint32_t small = h.cut() < 128 ? ~0u : 0u;   // its top bit is clear
+      uint32_t nr = 0;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const uint32_t x = rawx[v];
+        // top bit of a byte: low 7 bits of x >= those of cut, then x >= cut
+        const uint32_t t = (x | kTop) - cut_low;
+        const uint32_t ge = (x & t) | (small & (x | t));
+        // top bit clear: the byte's rank is kl (no carry crosses a byte)
+        const uint32_t e = out[v] ^ kl4;
+        const uint32_t ne = ((e & kLow) + kLow) | e;
+        const uint32_t right = (ge & ~ne & kTop) >> 7;
+        out[v] += right;
+        nr += (uint32_t)__popc(right);
+      }
+      // over the wave, in lane 63
+      int n = (int)nr;
+      n += __builtin_amdgcn_update_dpp(0, n, 0x111, 0xF, 0xF, true);
+      n += __builtin_amdgcn_update_dpp(0, n, 0x112, 0xF, 0xF, true);
+      n += __builtin_amdgcn_update_dpp(0, n, 0x114, 0xF, 0xF, true);
+      n += __builtin_amdgcn_update_dpp(0, n, 0x118, 0xF, 0xF, true);
+      n += __builtin_amdgcn_update_dpp(0, n, 0x142, 0xA, 0xF, true);
+      n += __builtin_amdgcn_update_dpp(0, n, 0x143, 0xC, 0xF, true);
+      if (lane == 63 && n) atomicAdd(&sh.nr[tree & 3], n);
+    }
+    if (bad & kTop) sh.dev_err = 1;
   };
   // partial sums of tree `tree` from the current residuals: per-lane private
   // LDS bins in kSets sets per lane (with two, the points of chunk positions
@@ -1107,23 +1535,41 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   // take several passes.  The wave that forms the total
   // of rank k posts it as word k of this workgroup's mailbox for the step
   // that decides the tree (buffer par, step number seq), and after the first
-  // bin barrier thread kBlock-1 posts the GROW right-count that route(tree)
-  // gathered as word L: no barrier stands between the totals and the post
-  // (only between passes).
+  // bin barrier one thread posts the GROW right-count of tree + 1 as word L
+  // (and, before the first tree of a run of steps, that of the tree itself as
+  // word L + 1): no barrier stands between the totals and the post (only
+  // between passes).
   // four sets with 8 chunks per thread (chains of 8 read-modify-writes
   // rather than 16: four chains 2547 -> 2562 chain-sweeps/s)
   constexpr int kSets = V >= 8 ? 4 : 2;
   constexpr int kRegRanks = kBinFloats / (kSets * kBlock);  // 32 or 16
   static_assert(kMaxLeaves % kRegRanks == 0 && kNullRank / kRegRanks >= kMaxLeaves / kRegRanks,
                 "the null rank must fall outside every bin pass");
-  auto reduce = [&](int tree, const uint32_t (&rks)[V], int par, uint32_t seq) {
-    const int L = sh.ctx[tree & (kRing - 1)].pr.L;
-    const int wl = wave * 64 + lane;
+  auto reduce = [&](int tree, int L, const uint32_t (&rks)[V], int par, uint32_t seq, bool first) {
+    const int wl = wv * 64 + lane;
     for (int base = 0; base < L; base += kRegRanks) {
       // the bin of rank k is k mod kRegRanks; a point outside the pass adds
       // 0 to its bin there (exact: a bin never holds -0).  Bins of different
       // sets never share an address, so a pair (one point of each set) is
       // read together and written together
+      if (mine && L <= kRegRanks) {
+        // one pass: a padding point adds its residual, 0, to some bin
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+          for (int b0 = 0; b0 < 4; b0 += kSets) {
+            float *q[kSets];
+            float cur[kSets];
+#pragma unroll
+            for (int e = 0; e < kSets; ++e)
+              q[e] = sh.bins + ((((rks[v] >> (8 * (b0 + e))) & (uint32_t)(kRegRanks - 1)) * kSets + e) *
+                                    kBlock + wl);
+#pragma unroll
+            for (int e = 0; e < kSets; ++e) cur[e] = *q[e];
+#pragma unroll
+            for (int e = 0; e < kSets; ++e) *q[e] = cur[e] + r[v][b0 + e];
+          }
+      } else if (mine)
 #pragma unroll
       for (int v = 0; v < V; ++v)
 #pragma unroll
@@ -1145,12 +1591,17 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
       if (base == 0) BART_CLOCK(clk, 9);
       lds_barrier();
       if (base == 0) BART_CLOCK(clk, 10);
-      if (base == 0 && t == kBlock - 1) {
-        // cleared for route(tree + 2), the next to count into this slot
-        post(A, sh, par, L, mk_word(seq, (uint64_t)sh.nr[tree & 1]));
-        sh.nr[tree & 1] = 0;
+      if (base == 0 && t == 64 * kPropWave) {
+        // cleared for the next trees to count into these slots
+        const int n1 = sh.nr[(tree + 1) & 3];
+        post(A, sh, par, L, mk_word(seq, pack_f64((double)n1)));
+        sh.nr[(tree + 1) & 3] = 0;
+        if (first) {
+          post(A, sh, par, L + 1, mk_word(seq, pack_f64((double)sh.nr[tree & 3])));
+          sh.nr[tree & 3] = 0;
+        }
       }
-      for (int k = base + wave; k < min(L, base + kRegRanks); k += kWaves) {
+      for (int k = base + wv; k < min(L, base + kRegRanks); k += kWaves) {
         // the kSets x 8 bins of this lane position (sets x waves): all read,
         // then cleared, then summed in a fixed tree
         double x[kSets * kWaves];
@@ -1171,31 +1622,48 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
       if (base + kRegRanks < L) lds_barrier();
     }
   };
-  // proposals of trees j0.. j0+2 into the ring, rank tables, rows of j0,
-  // route of j0, rows of j0+1, decision data of j0, partial sums of j0
-  // (posted for launch step `next`, which decides tree j0)
-  auto refill = [&](int j0, int64_t s, int next) {
-    for (int q = 0; q < 3; ++q)
+  // stored counts of the move of tree j: a GROW's node, a PRUNE's two leaves
+  auto load_move_counts = [&](int tree, const Head &h, int32_t &a, int32_t &b) {
+    const gptr<const int32_t> cnt = gbl((const int32_t *)A->count) + (int64_t)tree * 2 * A->H;
+    const int at = h.move() == kGrow ? h.eta() : (h.move() == kPrune ? 2 * h.eta() : 1);
+    a = cnt[at];
+    b = cnt[h.move() == kPrune ? at + 1 : at];
+  };
+  // scalars of trees j, j + 1 and j + 2
+  Head h0{}, h1{}, h2{};
+  // proposals of trees j0..j0+3 into the ring, rank tables of the first
+  // three, routes of j0 and j0+1, rows of j0+2, partial sums of j0 (posted for
+  // launch step `next`, which decides tree j0)
+  auto refill = [&](int j0, int next) {
+    for (int q = 0; q < 4; ++q)
       if (j0 + q < m) {
         const uint32_t wd = load_prop_word(A, j0 + q);
-        if (t < kPropWords) ((uint32_t *)&sh.ctx[(j0 + q) & (kRing - 1)].pr)[t] = wd;
+        if (t < kPropWords) ((uint32_t *)&ctx(j0 + q).pr)[t] = wd;
       }
     lds_barrier();
     for (int q = 0; q < 3; ++q)
-      if (j0 + q < m) build_ranks(A, sh.ctx[(j0 + q) & (kRing - 1)]);
+      if (j0 + q < m) build_ranks(A, ctx(j0 + q));
     lds_barrier();
-    issue_rows(j0);
-    const TdRegs tr0 = load_tree_data(A, sh.ctx[j0 & (kRing - 1)], j0, s);
-    route(j0, rk);
-    if (j0 + 1 < m) issue_rows(j0 + 1);
-    store_tree_data(sh.td[j0 & 1], sh.ctx[j0 & (kRing - 1)], tr0);
-    wait_vm_loads();  // the rows of j0 + 1 are in before the posts
-    reduce(j0, rk, next & 1, (uint32_t)next + 2);
+    h0 = read_head(ctx(j0));
+    issue_rows(j0, h0.axis());
+    route(j0, h0, rk);
+    if (j0 + 1 < m) {
+      h1 = read_head(ctx(j0 + 1));
+      issue_rows(j0 + 1, h1.axis());
+      route(j0 + 1, h1, rk1);
+    }
+    if (j0 + 2 < m) {
+      h2 = read_head(ctx(j0 + 2));
+      issue_rows(j0 + 2, h2.axis());
+    }
+    wait_vm_loads();  // the rows of j0 + 2 are in before the posts
+    reduce(j0, h0.L(), rk, next & 1, (uint32_t)next + 2, true);
   };
 
   // ---- prologue: proposals and normals of the first sweep, grid rendezvous
   int64_t s = Lc.s0;
   int j = Lc.j0;
+  int owner = j % G;  // workgroup that stores tree j
   if (j < m) {
     gen_proposals(A, seed, s, j);
     gen_normals(A, seed, s, j);
@@ -1207,71 +1675,101 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   // wave); the barrier orders the other waves after it
   if (t >= kBlock - 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   __syncthreads();
-  if (j < m && !sh.abort_flag) refill(j, s, 0);
+  // (flags read from LDS as scalars: a branch on a vector value would make
+  // the compiler keep every per-step scalar in vector registers and turn the
+  // loop's branches into exec masks)
+  auto aborted_now = [&]() { return __builtin_amdgcn_readfirstlane(sh.abort_flag) != 0; };
+  bool run = !aborted_now();
+  bool first = true;  // tree j is the first since the proposals were made
+  if (j < m && run) refill(j, 0);
 
 #pragma unroll 1
-  for (int step = 0; step < Lc.n_steps; ++step) {
-    if (sh.abort_flag) break;
+  for (int step = 0; run && step < Lc.n_steps; ++step) {
     asm volatile("" : "+v"(t));
     lane = t & 63;
-    wave = t >> 6;
     const uint32_t seq = (uint32_t)step + 2;
     const int par = step & 1;
     if (j < m) {
       // ================= tree step j =================
-      Ctx &c = sh.ctx[j & (kRing - 1)];
-      const int move = c.pr.move, eta = c.pr.eta, L = c.pr.L;
-      const int kl = c.pr.rank_l, kr = c.pr.rank_r;
+      // scalars again: where the paths of a step join, the compiler takes
+      // values that differ between paths as vector values
+      h0 = scalar(h0);
+      h1 = scalar(h1);
+      h2 = scalar(h2);
+      Ctx &c = ctx(j);
+      const int L = h0.L(), kl = h0.kl();
       const bool more1 = (j + 1 < m) && (step + 1 < Lc.n_steps);  // tree j+1 follows
-      const bool more2 = more1 && (j + 2 < m);
-      const bool more3 = more2 && (j + 3 < m);
-      // 1. route tree j+1 (its rows were loaded a step ago); this
-      //    workgroup's partial sums of tree j and its GROW right-count were
-      //    posted by the reduce that formed them
+      const bool have2 = j + 2 < m, have3 = j + 3 < m, have4 = j + 4 < m;
+      // 1. route tree j+2 (its rows were loaded a step ago); this
+      //    workgroup's partial sums of tree j and its GROW right-count of
+      //    tree j+1 were posted by the reduce that formed them
       clk = clock_slot(step);
       BART_CLOCK(clk, 0);
       BART_CLOCK_LAST(clk, 13);
-      if (more1) route(j + 1, rk2);
+      // tree j+3's, read ahead of the route that hides its latency
+      const Prop &p3 = ctx(have3 ? j + 3 : j).pr;
+      const Head raw3{p3.head0, p3.head1};
+      if (have2 && mine) route(j + 2, h2, rk2);
       BART_CLOCK(clk, 1);
       BART_CLOCK_LAST(clk, 14);
-      // 2. while the mailboxes fill: load rows of j+2, the decision data of
-      //    j+1 and the proposal of j+3
-      // (the small loads first: nothing waits behind the row loads)
-      const int j1 = more1 ? j + 1 : j, j3 = more3 ? j + 3 : j;
-      const TdRegs tdn = load_tree_data(A, sh.ctx[j1 & (kRing - 1)], j1, s);
-      const uint32_t pw3 = load_prop_word(A, j3);
+      // 2. while the mailboxes fill: load the rows of j+3; one wave the
+      //    proposal of j+4, and it builds the rank table of j+3; another the
+      //    decision data of j+1
+      const Head h3 = scalar(raw3);
+      uint32_t pw4 = 0;
+      ConstRegs cr{};
+      if (wv == kPropWave && have4)
+        pw4 = (gbl((const uint32_t *)(A->prop + j + 4)))[lane < kPropWords ? lane : 0];
+      if (wv == kConstWave && more1) cr = load_const(A, ctx(j + 1), h1, j + 1, s, lane);
+      int32_t cl1 = 0, cr1 = 0;  // counts of the move of j+1: its node's, or its children's
+      if (wv == kAcceptWave && more1) load_move_counts(j + 1, h1, cl1, cr1);
       BART_CLOCK_LAST(clk, 15);
-      if (more2) issue_rows(j + 2);
+      if (have3 && mine) issue_rows(j + 3, h3.axis());
       BART_CLOCK_LAST(clk, 16);
-      // 3. totals of tree j, in the same order in every workgroup: polls into
-      //    per-segment partials, then one wave reduces a word over the
-      //    segments with the fixed-order DPP tree (nseg <= 32 lanes).  The
-      //    polls run on the last waves; before the gather, wave 3 builds the
-      //    rank table of tree j+2 (its proposal was staged a step ago; 4
-      //    slots per lane) and wave 1 (waves 0-3 for large trees) computes
-      //    tree j's count-only constants
-      const int K = L + 1;
-      if (more2 && wave == 3)
+      if (wv == kPropWave && have3)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) build_rank_slot(A, sh.ctx[(j + 2) & (kRing - 1)], 64 * i + lane);
-      pre_decide(A, sh, c, sh.td[j & 1], w == 0 ? uncounted : -1);
+        for (int i = 0; i < 4; ++i) build_rank_slot(A, ctx(j + 3), 64 * i + lane);
       BART_CLOCK(clk, 2);
-      const int nseg = gather_polls(A, sh, par, seq, K, L, Lc.spin_limit, clk);
+      // 3. the grid's sums of tree j and right-count of tree j+1, in the same
+      //    order in every workgroup
+      const Gathered ga =
+          scalar(gather_rows(A, sh, par, seq, L + (first ? 2 : 1), Lc.spin_limit, wv, clk));
       BART_CLOCK(clk, 3);
-      decide_step(A, sh, c, sh.td[j & 1], nseg);
+      // set before the barrier of the gather only; read here, it is waited
+      // for together with the decision's words
+      const bool aborted = aborted_now();
+      if (first) {
+        // the constants of the first tree, which no earlier step made
+        if (wv == kAcceptWave || wv == kConstWave) {
+          const double n_right = gathered(sh, ga, L + 1);
+          if (wv == kConstWave) {
+            const ConstRegs c0 = load_const(A, c, h0, j, s, lane);
+            draw_consts(A, sh, tconst(j), c, h0, j, s, c0, n_right);
+          } else if (h0.move() != kNone) {
+            int32_t a = 0, b = 0;
+            load_move_counts(j, h0, a, b);
+            const double nr = h0.move() == kGrow ? n_right : (double)b;
+            accept_consts(A, sh, tconst(j), c, h0, h0.move() == kGrow ? (double)a - nr : (double)a, nr);
+          }
+        }
+        lds_barrier();
+        first = false;
+      }
+      double n_right1 = 0.0;  // read before the next sums replace it
+      if ((wv == kAcceptWave || wv == kConstWave) && more1) n_right1 = gathered(sh, ga, L);
+      const Decision d = decide_all(A, sh, c, tconst(j), h0, ga, wv == kStoreWave, tracing);
       BART_CLOCK(clk, 4);
-      // stage what later trees need
-      if (more3 && t < kPropWords) ((uint32_t *)&sh.ctx[(j + 3) & (kRing - 1)].pr)[t] = pw3;
-      if (more1) store_tree_data(sh.td[(j + 1) & 1], sh.ctx[(j + 1) & (kRing - 1)], tdn);
-      lds_barrier();
-      BART_CLOCK(clk, 5);
-      wait_vm_loads();  // the rows of j+2 are in before this step's stores
+      if (aborted) {
+        run = false;
+        break;
+      }
+      if (wv == kPropWave && have4 && lane < kPropWords)
+        ((uint32_t *)&ctx(j + 4).pr)[lane] = pw4;
+      wait_vm_loads();  // the rows of j+3 are in before this step's stores
       // 4. residuals and index row (item 11): the delta of every rank is
       //    final (a point in a child of eta of a merged move takes the
       //    merged value); such a point also takes the index eta
-      const int flags = sh.flags, acc = flags & 1, merged = (flags >> 1) & 1;
-      const bool changed = acc && move != kNone;
-      const gptr<ChunkT> row = gbl((ChunkT *)((char *)A->idx + (int64_t)j * A->ldi * IB));
+      if (mine) {
       float dl[V][4];
 #pragma unroll
       for (int v = 0; v < V; ++v)
@@ -1281,7 +1779,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
       for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int b = 0; b < 4; ++b) r[v][b] += dl[v][b];
-      if (changed) {
+      if (d.acc) {
+        const gptr<ChunkT> row = gbl((ChunkT *)((char *)A->idx + (int64_t)j * A->ldi * IB));
 #pragma unroll
         for (int v = 0; v < V; ++v) {
           bool touch = false;
@@ -1294,36 +1793,59 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
 #pragma unroll
           for (int b = 0; b < 4; ++b) {
             const int rnk = (rk[v] >> (8 * b)) & 0xff;
-            const bool pair = (rnk == kl) || (rnk == kr);
+            const bool pair = (rnk == kl) || (rnk == kl + 1);
             touch |= pair;
-            out = IC::put(out, b, (merged && pair) ? eta : hs[b]);
+            out = IC::put(out, b, (d.merged && pair) ? h0.eta() : hs[b]);
           }
           // only an existing chunk has a point of the move's pair
           if (touch) row[(w * V + v) * kBlock + t] = out;
         }
       }
-      BART_CLOCK(clk, 6);
-      finish_tree(A, Lc, sh, c, j, s, step);
-      uncounted = j;
-      BART_CLOCK(clk, 7);
-      // 5. tree j+1: partial sums from the updated residuals
-      if (more1) {
-        reduce(j + 1, rk2, (step + 1) & 1, (uint32_t)step + 3);
-#pragma unroll
-        for (int v = 0; v < V; ++v) rk[v] = rk2[v];
-      } else {
-        lds_barrier();
       }
-      BART_CLOCK(clk, 8);
+      BART_CLOCK(clk, 5);
+      // 5. tree j+1: partial sums from the updated residuals
+      if (more1)
+        reduce(j + 1, h1.L(), rk1, (step + 1) & 1, (uint32_t)step + 3, false);
+      else
+        lds_barrier();
+      // 6. behind the posts, on the waves with the fewest totals: the
+      //    constants of tree j+1, then the owner's store of tree j, and the
+      //    move statistics
+      if (wv == kConstWave) {
+        if (more1)
+          draw_consts(A, sh, tconst(j + 1), ctx(j + 1), h1, j + 1, s, cr, n_right1);
+      } else if (wv == kAcceptWave && more1 && h1.move() != kNone) {
+        const double nr = h1.move() == kGrow ? n_right1 : (double)cr1;
+        accept_consts(A, sh, tconst(j + 1), ctx(j + 1), h1,
+                      h1.move() == kGrow ? (double)cl1 - nr : (double)cl1, nr);
+      } else if (wv == kStoreWave && owner == w) {
+        store_tree(A, sh, c, tconst(j), h0, d, j);
+      }
+      if (w == 0 && wv == kPropWave && lane < 6) {
+        const int grow = h0.move() == kGrow, prune = h0.move() == kPrune;
+        const int add[6] = {grow, prune, grow & d.acc, prune & d.acc, 1, L - d.merged};
+        int x = add[0];
+#pragma unroll
+        for (int q = 1; q < 6; ++q) x = lane == q ? add[q] : x;
+        sh.stats[lane] += (uint64_t)x;
+      }
+      if (++owner == G) owner = 0;
+      if (tracing && j % G == w) trace_tree_step(Lc.trace + step, sh, c, j, s, A->H);
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        rk[v] = rk1[v];
+        rk1[v] = rk2[v];
+      }
+      h0 = h1;
+      h1 = h2;
+      h2 = h3;
+      BART_CLOCK(clk, 6);
       BART_CLOCK_LAST(clk, 12);
       ++j;
     } else {
       // ================= sigma^2 step (sec. 3.3, "Sampling the error variance")
       clk = -1;
       BART_SCLOCK(0);
-      if (w == 0 && t == kBlock - 1 && uncounted >= 0)
-        count_move(sh, sh.ctx[uncounted & (kRing - 1)]);
-      uncounted = -1;
       __syncthreads();  // this workgroup's tree writes are visible to all its threads
       double ssr = 0.0;
 #pragma unroll
@@ -1334,16 +1856,19 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
           ssr += x * x;
         }
       ssr = wave_total63(ssr);
-      if (lane == 63) sh.wave_part[wave] = ssr;
+      if (lane == 63) sh.wave_part[wv] = ssr;
       sigma2_tail(A, Lc, sh, s, step, seq, par);
       if (A->probit)
 #pragma unroll
         for (int v = 0; v < V; ++v)
           if (const uint32_t ok = ok4(v)) latent_chunk(A, seed, s, (w * V + v) * kBlock + t, ok, r[v]);
       j = 0;
+      owner = 0;
       ++s;
+      first = true;
+      run = !aborted_now();
       BART_SCLOCK(7);
-      if (step + 1 < Lc.n_steps && !sh.abort_flag) refill(0, s, step + 1);
+      if (step + 1 < Lc.n_steps && run) refill(0, step + 1);
       BART_SCLOCK(8);
     }
   }
@@ -1359,8 +1884,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
       q[2] = r[v][2];
       q[3] = r[v][3];
     }
-  if (w == 0 && t == kBlock - 1 && uncounted >= 0)
-    count_move(sh, sh.ctx[uncounted & (kRing - 1)]);
   __syncthreads();
   if (w == 0 && t < 6) A->ctl->stats[t] += sh.stats[t];
   if (t == 0 && (sh.abort_flag || sh.dev_err))
@@ -1546,7 +2069,7 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
     const gptr<ChunkT> rowa = row_of(do_a ? ja : 0);
     const gptr<ChunkT> rown = row_of(do_n ? jn : 0);
     const bool trav = CF && do_n && lo == 0;  // Algorithm 1 for tree jn
-    const NodeList &nn = sh.nl[(jn < 0 ? 0 : jn) & (kRing - 1)];
+    const NodeList &nn = sh.nl[(jn < 0 ? 0 : jn) & (kNodeRing - 1)];
     // without an index cache: tree jn's internal-node count, its mask of
     // internal heap slots and its first 8 nodes (predictor-row offset, cut,
     // heap slot), out of LDS once per pass rather than per batch
@@ -1668,7 +2191,7 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
 #pragma unroll
             for (int u = 0; u < U; ++u) wd[e][u] = 0u;
             if (k0 + e < ni) {
-              const int64_t off = k0 == 0 ? xoff8[e] : (int64_t)cn.ax[nn.nh[k0 + e]] * A->ldx;
+              const int64_t off = k0 == 0 ? xoff8[e] : (int64_t)nn.ax[nn.nh[k0 + e]] * A->ldx;
               const gptr<const uint32_t> xr = gbl((const uint32_t *)(A->X + off));
 #pragma unroll
               for (int u = 0; u < U; ++u) wd[e][u] = xr[cu[u]];
@@ -1679,7 +2202,7 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
             const int k = k0 + e;
             const int hk = k0 == 0 ? slot8[e] : (k < ni ? (int)nn.nh[k] : 0);
             // no bit past the last node
-            const int cv = k0 == 0 ? cut8[e] : (k < ni ? (int)cn.ct[hk] : 256);
+            const int cv = k0 == 0 ? cut8[e] : (k < ni ? (int)nn.ct[hk] : 256);
             const int pos = by_slot ? hk : (k & 31);
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -1738,17 +2261,17 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
               const int h = hh[u][b];
-              const int cv = h < H ? cn.ct[h] : 0;
+              const int cv = h < H ? nn.ct[h] : 0;
               xb[u][b] = 0;
               if (((ok[u] >> b) & 1u) && cv)
-                xb[u][b] = gbl(A->X)[(int64_t)cn.ax[h] * A->ldx + 4 * (int64_t)ch[u] + b];
+                xb[u][b] = gbl(A->X)[(int64_t)nn.ax[h] * A->ldx + 4 * (int64_t)ch[u] + b];
             }
 #pragma unroll
           for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
               const int h = hh[u][b];
-              const int cv = h < H ? cn.ct[h] : 0;
+              const int cv = h < H ? nn.ct[h] : 0;
               if (cv) hh[u][b] = 2 * h + (xb[u][b] >= cv ? 1 : 0);
             }
         }
@@ -1936,7 +2459,7 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
     const int64_t o = (int64_t)tree * H + h;
     return (uint32_t)gbl(A->axis)[o] | ((uint32_t)gbl(A->cut)[o] << 16);
   };
-  auto store_struct = [&](Ctx &c, uint32_t wv) {
+  auto store_struct = [&](NodeList &c, uint32_t wv) {
     if (t < A->H) {
       c.ax[t] = (uint16_t)(wv & 0xffffu);
       c.ct[t] = (uint8_t)(wv >> 16);
@@ -1949,13 +2472,13 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
       if (j0 + q < m) {
         const uint32_t wd = load_prop_word(A, j0 + q);
         if (t < kPropWords) ((uint32_t *)&sh.ctx[(j0 + q) & (kRing - 1)].pr)[t] = wd;
-        if (CF) store_struct(sh.ctx[(j0 + q) & (kRing - 1)], struct_word(j0 + q));
+        if (CF) store_struct(sh.nl[(j0 + q) & (kNodeRing - 1)], struct_word(j0 + q));
       }
     lds_barrier();
     for (int q = 0; q < 3; ++q)
       if (j0 + q < m) {
         build_ranks(A, sh.ctx[(j0 + q) & (kRing - 1)]);
-        if (CF) build_inodes(A, sh.ctx[(j0 + q) & (kRing - 1)], sh.nl[(j0 + q) & (kRing - 1)]);
+        if (CF) build_inodes(A, sh.nl[(j0 + q) & (kNodeRing - 1)]);
       }
     lds_barrier();
     const TdRegs tr0 = load_tree_data(A, sh.ctx[j0 & (kRing - 1)], j0, s);
@@ -2027,13 +2550,13 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
         asm volatile("" ::"v"(touch[u][0]), "v"(touch[u][1]), "v"(touch[u][2]));
       decide_step(A, sh, c, sh.td[j & 1], nseg);
       if (more3 && t < kPropWords) ((uint32_t *)&sh.ctx[(j + 3) & (kRing - 1)].pr)[t] = pw3;
-      if (CF && more3) store_struct(sh.ctx[(j + 3) & (kRing - 1)], sw3);
+      if (CF && more3) store_struct(sh.nl[(j + 3) & (kNodeRing - 1)], sw3);
       if (more1) store_tree_data(sh.td[(j + 1) & 1], sh.ctx[(j + 1) & (kRing - 1)], tdn);
       lds_barrier();
       finish_tree(A, Lc, sh, c, j, s, step);
       uncounted = j;
       if (more3) build_ranks(A, sh.ctx[(j + 3) & (kRing - 1)]);
-      if (CF && more3) build_inodes(A, sh.ctx[(j + 3) & (kRing - 1)], sh.nl[(j + 3) & (kRing - 1)]);
+      if (CF && more3) build_inodes(A, sh.nl[(j + 3) & (kNodeRing - 1)]);
       have_ssr = j == m - 1;
       pass_all(j, more1 ? j + 1 : -1, have_ssr, (step + 1) & 1, (uint32_t)step + 3);
       ++j;

@@ -2,16 +2,13 @@
 the diagnostic build libbart_clocks.so (build.build(clocks=True)).
 
 Thread 0 of every workgroup stamps the wall clock (100 MHz) at the phase
-boundaries of 64 consecutive tree steps of one launch, and every workgroup
+boundaries of 32 consecutive tree steps of one launch, and every workgroup
 counts the mailbox loads its polls issue.  Phases of a tree step j:
-  route      route of tree j+1 (rank of every point in its larger tree)
-  prefetch   loads of later trees' rows and decision data, rank table of
-             tree j+2, tree j's count-only constants
+  route      route of tree j+2 (rank of every point in its larger tree)
+  prefetch   loads of later trees' rows
   gather     polls of every workgroup's partial sums of tree j
-  decide     MH decision and leaf draws (wave 0: the decision)
-  barrier    until every wave has its part of the decision
+  decide     MH decision and leaf draws (every wave)
   update     residual update and index-row rewrite
-  finish     the owner's write of tree j
   reduce     partial sums of tree j+1 and their post (split into the bin
              updates, the bin barrier, rank 0's cross-wave total and post,
              and the rest)
@@ -35,10 +32,11 @@ import numpy as np
 HERE = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, os.path.dirname(HERE))
 
-K_GRID, K_STEPS, K_PH = 256, 48, 20  # kMaxGrid, kClockSteps, kClockPh
+K_GRID, K_STEPS, K_PH = 256, 32, 20  # kMaxGrid, kClockSteps, kClockPh
 K_START = 205                        # kClockStart
 K_SPH = 9                            # kSigmaPh
-PHASES = ["route", "prefetch", "gather", "decide", "barrier", "update", "finish", "reduce"]
+PHASES = ["route", "prefetch", "gather", "decide", "update", "reduce"]
+END = len(PHASES)  # stamp at the end of a step
 # stamps 9-11 (inside the reduce: bins done, bin barrier passed, rank 0 posted)
 SUB = ["bins", "bin barrier", "rank-0 total and post", "rest of reduce"]
 
@@ -74,17 +72,17 @@ def run(config: int, warmup: int, seed: int, out: str | None) -> dict:
         np.save(out, ts)
     loads = ts[:, :, K_PH - 1]
     clk = ts[:, :, : K_PH - 1] * 10  # ns
-    sub = clk[:, :, [7, 9, 10, 11, 8]]  # finish, bins, barrier, rank-0 post, end
-    ok = (clk[:, :, 0] > 0).all(0) & (clk[:, :, 8] > 0).all(0)  # tree steps (not sigma^2)
+    sub = clk[:, :, [END - 1, 9, 10, 11, END]]  # update, bins, barrier, rank-0 post, end
+    ok = (clk[:, :, 0] > 0).all(0) & (clk[:, :, END] > 0).all(0)  # tree steps (not sigma^2)
     clk, loads, sub = clk[:, ok], loads[:, ok], sub[:, ok]
-    d = np.diff(clk[:, :, :9], axis=2)
+    d = np.diff(clk[:, :, :END + 1], axis=2)
     ds = np.diff(sub, axis=2)
     res = {"config": config, "workload": inp.workload, "grid": G, "tree_steps": int(ok.sum()),
            "first_step": K_START,
            "phase_median_ns": {p: float(np.median(d[:, :, k])) for k, p in enumerate(PHASES)},
            "phase_p90_ns": {p: float(np.percentile(d[:, :, k], 90)) for k, p in enumerate(PHASES)},
            "reduce_parts_median_ns": {p: float(np.median(ds[:, :, k])) for k, p in enumerate(SUB)}}
-    post, gd = clk[:, :, 8], clk[:, :, 3]
+    post, gd = clk[:, :, END], clk[:, :, 3]
     res["step_period_median_ns"] = float(np.median(np.diff(clk[0, :, 0])))
     res["post_spread_median_ns"] = float(np.median(post.max(0) - post.min(0)))
     last = post[:, :-1].max(0)

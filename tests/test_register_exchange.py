@@ -1,0 +1,83 @@
+"""The register kernel's exchange and decision at the edges of their branches,
+in lockstep with the oracle: words per tree at and around the powers of two
+that set the lanes per workgroup (7, 8, 15, 16, 31, 32, 63 and 64 leaves, one
+and two more with the right-counts), 128 leaves (more words than a wave has
+lanes), and numbers of workgroups around those that set the polling waves;
+runs of steps that start inside a sweep (the first tree of a run makes its own
+constants) and end right before and at its last trees; and cuts on both sides
+of 128, where the byte compare of the route changes form."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2410_23244_amd.inputs import make_inputs
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _state(inp, leaves, rng):
+    """Trees of `leaves` leaves each (the leftmost growable node splits first),
+    with random axes and cuts, as a state for set_state."""
+    m, H, n = inp.m, 1 << (inp.D - 1), inp.n
+    axis, cut = np.zeros((m, H), np.uint16), np.zeros((m, H), np.uint8)
+    leaf, idx = np.zeros((m, 2 * H), np.float32), np.zeros((m, n), np.uint8)
+    f = np.zeros(n)
+    for j in range(m):
+        for h in range(1, leaves):  # heap order: nodes 1..leaves-1 are internal
+            axis[j, h] = rng.integers(inp.p)
+            cut[j, h] = rng.integers(1, inp.n_cuts[axis[j, h]] + 1)
+        leaf[j] = rng.normal(0.0, inp.hyper.sigma_mu, 2 * H)
+        hh = np.ones(n, np.int64)
+        for _ in range(inp.D - 1):
+            inner = (hh < H) & (cut[j, np.minimum(hh, H - 1)] > 0)
+            q = np.where(inner, hh, 0)
+            right = inp.X_b[axis[j, q], np.arange(n)] >= cut[j, q]
+            hh = np.where(inner, 2 * hh + right, hh)
+        idx[j] = hh
+        f += leaf[j, hh].astype(np.float64)
+    resid = (inp.y_c.astype(np.float64) - f).astype(np.float32)
+    return dict(axis=axis, cut=cut, leaf=leaf, idx=idx, resid=resid,
+                sigma2=inp.hyper.sigma2_init, sweep=0, next=0)
+
+
+def _run(inp, grid, leaves, steps):
+    from paper_2410_23244_amd.bart import BART_RESID_REGISTERS, from_inputs
+
+    g = from_inputs(inp, grid=grid, residency=BART_RESID_REGISTERS)
+    print(f"leaves={leaves} grid={g.launch_info().grid} V={g.launch_info().chunks_per_thread}",
+          flush=True)
+    g.set_state(_state(inp, leaves, np.random.default_rng(leaves)))
+    done = 0
+    for k in steps:
+        rep = parity.lockstep(inp, g, seed=11, warm_sweeps=0, n_steps=k)
+        done += rep.moves
+    assert done > 0 and g.status() == 0
+
+
+@pytest.mark.parametrize("leaves", [1, 6, 7, 8, 14, 15, 16, 30, 31, 32, 62, 63, 64, 127, 128])
+def test_words_per_tree(leaves):
+    inp = make_inputs(5, n=9001, p=30, m=5, D=8)
+    _run(inp, 5, leaves, [2 * (inp.m + 1)])
+
+
+@pytest.mark.parametrize("grid", [1, 2, 3, 8, 9, 16, 17, 64, 65, 129, 256])
+def test_workgroups(grid):
+    inp = make_inputs(2, n=2003, p=30, m=7, D=6)
+    for leaves in (4, 12, 24):
+        _run(inp, grid, leaves, [2 * (inp.m + 1)])
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 6])
+def test_runs_that_start_and_end_inside_a_sweep(m):
+    inp = make_inputs(2, n=5003, p=20, m=m, D=6)
+    _run(inp, 4, 5, [1, 1, 2, 3, 1, 4, m + 1, 5])
+
+
+@pytest.mark.parametrize("n", [40003, 140003, 300007])
+def test_chunks_per_thread(n):
+    # 1, 2 and 4 chunks per thread on at most 41 workgroups
+    inp = make_inputs(2, n=n, p=20, m=5, D=6)
+    grid = {40003: 20, 140003: 35, 300007: 41}[n]
+    _run(inp, grid, 9, [inp.m + 1])
