@@ -426,6 +426,9 @@ SweepArgs make_args(bart_handle *h, int ch) {
   A.D = c.max_depth;
   A.H = h->H;
   A.p_nz = h->p_nz;
+  A.cuts_all = h->n_cuts[0];
+  for (int32_t k : h->n_cuts)
+    if (k != A.cuts_all) A.cuts_all = 0;
   A.G = h->G;
   A.chunks = (int32_t)h->chunks;
   A.cpt = h->V;

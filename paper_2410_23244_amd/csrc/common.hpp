@@ -78,7 +78,8 @@ struct SweepArgs {
   int32_t chain;  // index of this chain in the launch
   float *latent;        // probit: [n_pad] latents of this chain
   const uint8_t *ybin;  // probit: [n_pad] binary response (shared)
-  int32_t probit, pad2_;
+  int32_t probit;
+  int32_t cuts_all;  // the cut count that every axis has, or 0 where they differ
   double probit_offset;
   double alpha, beta, mu_mu, sigma_mu, nu, lambda, p_grow;
 };

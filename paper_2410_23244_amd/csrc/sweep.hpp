@@ -456,8 +456,18 @@ __device__ __noinline__ void gen_proposals(const SweepArgs *__restrict__ A, uint
                                            int j0) {
   const Key key = chain_key(seed, A->chain);
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  for (int tr = wg_id(A) + A->G * wv; tr < A->m; tr += A->G * kWaves)
-    if (tr >= j0) propose_tree(A, key, tr, s, A->prop[tr]);
+  const int step = A->G * kWaves;
+  int tr = wg_id(A) + A->G * wv;
+  while (tr < j0) tr += step;
+  if (tr >= A->m) return;
+  const double split = split_prob_of_lane(A);
+  TreeWords tw = load_tree(A, tr);
+  for (; tr < A->m; tr += step) {
+    // the next tree of this wave is on its way while this one is proposed
+    const TreeWords next = load_tree(A, min(tr + step, A->m - 1));
+    propose_tree(A, key, tr, s, tw, split, A->prop[tr]);
+    tw = next;
+  }
 }
 
 // sigma^2 | rest ~ InvGamma((nu+n)/2, (nu lambda + SSR)/2), the conjugate
@@ -942,11 +952,14 @@ __device__ __forceinline__ void sigma2_tail(const SweepArgs *__restrict__ A, con
   // others propose
   if (!A->probit && t == kBlock - 64) sh.sig_gamma = sigma2_gamma(A, seed, s);
   // the next sweep's proposals (owners) and normals, published by the
-  // release below together with this sweep's tree writes
+  // release below together with this sweep's tree writes; behind the last
+  // step of a launch nobody reads them (a launch makes those of its first
+  // sweep itself, as its seed may be another)
+  const bool next_sweep = step + 1 < Lc.n_steps;
   BART_SCLOCK(1);
-  gen_proposals(A, seed, s + 1, 0);
+  if (next_sweep) gen_proposals(A, seed, s + 1, 0);
   BART_SCLOCK(2);
-  gen_normals(A, seed, s + 1, 0);
+  if (next_sweep) gen_normals(A, seed, s + 1, 0);
   BART_SCLOCK(3);
   __syncthreads();
   BART_SCLOCK(4);
@@ -1005,7 +1018,7 @@ __device__ __forceinline__ void sigma2_tail(const SweepArgs *__restrict__ A, con
 // ------------------------------------------------------- register kernel
 // The decision of a tree step as the register kernel takes it.  All of it
 // that depends on counts alone (sec. 3.3 items 4, 5, 8) is made a step ahead
-// by one wave (decide_consts): a tree is routed two steps before its own, so
+// by two waves (draw_consts, accept_consts): a tree is routed two steps before its own, so
 // its GROW right-count travels with the sums of the tree before it.  What is
 // left when the sums arrive is a dozen dependent fp64 operations, and every
 // wave takes them for itself (decide_all) from the same words: no barrier
