@@ -224,6 +224,7 @@ struct Ctx {
   uint8_t heap_of[256];   // rank -> heap slot; 0 from kNullRank on
 };
 
+constexpr int kTabNodes = 6;
 // Without an index cache: a tree snapshot and its internal nodes, by ring slot.
 struct NodeList {
   uint16_t ax[kMaxLeaves];   // axis and cut per internal heap slot, for Algorithm 1
@@ -231,6 +232,8 @@ struct NodeList {
   uint64_t imask;            // internal heap slots below 64
   uint16_t axis8[8];         // axis and cut of the first 8 internal nodes
   uint8_t cut8[8];
+  uint8_t tab[1 << kTabNodes];  // at most kTabNodes internal nodes: leaf by their decisions
+                                // (the first node's the highest bit)
   uint8_t nidx[kMaxLeaves];  // heap slot -> index among the internal nodes (kNoNode: none)
   uint8_t nh[kMaxLeaves];    // heap slot of the k-th internal node, in heap order
   int32_t ni;                // internal nodes
@@ -363,6 +366,7 @@ __device__ __forceinline__ void build_inodes(const SweepArgs *__restrict__ A, No
   if ((t >> 6) != 4) return;
   const int H = A->H;
   int base = 0;
+  uint64_t inner[2] = {0, 0};
   for (int h0 = 0; h0 < H; h0 += 64) {
     const int h = h0 + lane;
     const bool in = h >= 1 && h < H && nl.ct[h] != 0;
@@ -376,9 +380,21 @@ __device__ __forceinline__ void build_inodes(const SweepArgs *__restrict__ A, No
       nl.cut8[k] = nl.ct[h];
     }
     if (h0 == 0 && lane == 0) nl.imask = bal;
+    inner[h0 >> 6] = bal;
     base += __popcll(bal);
   }
   if (lane == 0) nl.ni = base;
+  if (base <= kTabNodes) {  // lane l: the leaf that decisions l reach
+    int h = 1;
+    for (int lvl = 1; lvl < A->D; ++lvl) {
+      const uint64_t w = h < 64 ? inner[0] : inner[1];
+      if (h < H && ((w >> (h & 63)) & 1ull)) {
+        const int k = __popcll(w & ((1ull << (h & 63)) - 1ull)) + (h < 64 ? 0 : __popcll(inner[0]));
+        h = 2 * h + ((lane >> (base - 1 - k)) & 1);
+      }
+    }
+    nl.tab[lane] = (uint8_t)h;
+  }
 }
 
 // Thread that loads and stages the decision data of the move's node eta: in
@@ -2174,7 +2190,51 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
           rn[u] = (ChunkT)0;
           rv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-      if (trav && ni_p <= 32) {
+      if (trav && ni_p <= kTabNodes) {
+        // leaves of tree jn: the decision of every internal node for the
+        // chunk's 4 points, from one coalesced word of the node's predictor
+        // row (all nodes' words in flight at once), shifted into a number per
+        // point, and the leaf that Algorithm 1 reaches by these decisions from
+        // the tree's table (two instructions per decision and a table read,
+        // where masks and a descent in registers took about 4 per decision
+        // and 30 per point: n = 1e6 2,050 -> 1,870 us a sweep, n = 5e6 1,677
+        // -> 1,351; six nodes cover nearly all trees the sampler grows, and
+        // each more doubles the table)
+        uint32_t cu[U], code[U][4], wd[kTabNodes][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          cu[u] = ok[u] ? ch[u] : 0u;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) code[u][b] = 0u;
+        }
+#pragma unroll
+        for (int e = 0; e < kTabNodes; ++e) {
+          if (e < ni_p) {
+            const gptr<const uint32_t> xr = gbl((const uint32_t *)(A->X + xoff8[e]));
+#pragma unroll
+            for (int u = 0; u < U; ++u) wd[e][u] = xr[cu[u]];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < kTabNodes; ++e) {
+          if (e < ni_p) {
+            const uint32_t below = (uint32_t)cut8[e] - 1u;  // byte >= cut: below - byte < 0
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+              for (int b = 0; b < 4; ++b)
+                code[u][b] = __builtin_amdgcn_alignbit(code[u][b], below - ((wd[e][u] >> (8 * b)) & 0xffu), 31);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          ChunkT pk = 0;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) pk = IC::put(pk, b, ((ok[u] >> b) & 1u) ? (int)nn.tab[code[u][b]] : 0);
+          rn[u] = pk;
+          if (!ST && ok[u]) rown[ch[u]] = pk;
+        }
+      } else if (trav && ni_p <= 32) {
         // leaves of tree jn by Algorithm 1 on its structure snapshot: the
         // decision of every internal node for the chunk's 4 points, from one
         // coalesced word of the node's predictor row (the words of up to 8
