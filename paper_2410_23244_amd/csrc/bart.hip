@@ -505,20 +505,24 @@ void launch_predict(bart_handle *h, const uint8_t *Xt, int64_t ldx, int64_t nt, 
   k_pred_program<<<dim3(ngroups, h->nchain), 64 * kPredTrees, 0, h->stream>>>(
       axis, cut, leaf, prog, m, p, D, h->H, cb);
   constexpr int64_t kWaveLds = kPredTrees * kPredTab * sizeof(float);
-  const int64_t want = 8 * (int64_t)h->cus;
-  const int64_t words = (nt + 255) / 256;
-  if ((words + 1) / 2 * h->nchain >= want) {
-    const int64_t tiles = (words + 1) / 2;
-    k_pred_eval<2, ACC><<<dim3(grid_for(tiles, 4), h->nchain), 256, 4 * kWaveLds, h->stream>>>(
-        Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups, D, h->H, offset, cb, 1, out, sum, sumsq);
-    return;
-  }
+  // Four waves of a block share a tile's groups of trees wherever there are
+  // as many: a wave's batches are one chain of loads, and short chains over
+  // more tiles in flight keep the vector units busier than a tile per wave
+  // (us, 200 trees, 1 / 4 / 8 waves a tile: 3e5 points 79 / 38 / 38, 5.2e5
+  // 83 / 54 / 56, 1e6 111 / 90 / 100, 3e6 262 / 244 / 284; two words per lane
+  // and a tile per wave 103, 106, 118 and 258).  Up to 16 while the launch has
+  // fewer than 8 waves per compute unit (1e5 points, 4 / 8 waves: 25 / 21;
+  // 1,000 trees of depth 8 122 / 86, and on inputs not in the caches 89 with 8
+  // against 97 with 16).
+  const int64_t tiles = (nt + kPredTile - 1) / kPredTile;
   int split = 1;
-  while (split < 16 && 2 * split <= ngroups && words * h->nchain * split < want) split *= 2;
+  while (split < 16 && 2 * split <= ngroups &&
+         (split < 4 || tiles * h->nchain * split < 8 * (int64_t)h->cus))
+    split *= 2;
   const int nw = split > 1 ? split : 4;
-  k_pred_eval<1, ACC><<<dim3(grid_for(words, split > 1 ? 1 : 4), h->nchain), 64 * nw,
-                        nw * kWaveLds, h->stream>>>(Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups,
-                                                    D, h->H, offset, cb, split, out, sum, sumsq);
+  k_pred_eval<ACC><<<dim3(grid_for(tiles, split > 1 ? 1 : 4), h->nchain), 64 * nw, nw * kWaveLds,
+                     h->stream>>>(Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups, D, h->H, offset,
+                                  cb, split, out, sum, sumsq);
 }
 
 }  // namespace

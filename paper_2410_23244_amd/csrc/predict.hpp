@@ -21,6 +21,7 @@ constexpr int kPredTabNodes = 6;    // most internal nodes of a tree with a deci
 constexpr int kPredTab = 1 << kPredTabNodes;
 constexpr int kPredListNodes = 31;  // most internal nodes of a tree with a leaf bit mask
 constexpr int kPredBatch = 8;       // nodes whose predictor words are in flight together
+constexpr int kPredTile = 256;      // points per tile: 4 per lane
 constexpr uint32_t kPredNop = 256u << 16;  // a decision no byte takes
 
 // One group of the program.
@@ -176,59 +177,54 @@ __device__ __forceinline__ void pred_decide4(uint32_t (&code)[4], uint32_t x, ui
       : "v"(x), "s"(cut));
 }
 
-// The compiled trees at a tile of 64 x 4 W points per wave: word u of lane l
-// holds the 4 points at 4 (64 (W tile + u) + l).  split = 1: every wave has a
-// tile of its own.  Else the waves of a block share one tile and the groups
-// of trees, in order, among them, and their fp64 sums are added in that
-// order.  blockIdx.y = chain.  ACC: add f and f^2 (fp64) to sum and sumsq
-// instead of writing fp32(f) to out.
+// The compiled trees at a tile of 64 x 4 points per wave: lane l's word holds
+// the 4 points at 4 (64 tile + l).  split = 1: every wave has a tile of its
+// own.  Else the waves of a block share one tile and the groups of trees, in
+// order, among them, and their fp64 sums are added in that order.
+// blockIdx.y = chain.  ACC: add f and f^2 (fp64) to sum and sumsq instead of
+// writing fp32(f) to out.  What bounds it is the issue of the decisions, two
+// instructions each per point, then the words' loads: 1e6 points, 200 trees,
+// 402 us by Algorithm 1, 90 us here.
 typedef uint32_t u32_any __attribute__((aligned(1)));  // Xt has no alignment of its own
 template <class T>
 using cptr = const __attribute__((address_space(4))) T *;  // scalar loads
 
-template <int W, bool ACC>
+template <bool ACC>
 __global__ void __launch_bounds__(1024)
     k_pred_eval(const uint8_t *Xt, int64_t ldx, int64_t nt, int p, const PredGroup *prog0,
                 const uint16_t *axis0, const uint8_t *cut0, const float *leaf0, int ngroups, int D,
                 int H, double offset, size_t chain_bytes, int split, float *out0, double *sum0,
                 double *sumsq0) {
   extern __shared__ __align__(16) char s_raw[];
-  constexpr size_t kWaveLds = kPredTrees * kPredTab * sizeof(float);  // also 64 x 4 W fp64
-  static_assert(kWaveLds >= 64 * 4 * W * sizeof(double), "the partial sums reuse the tables");
+  constexpr size_t kWaveLds = kPredTrees * kPredTab * sizeof(float);  // also 64 x 4 fp64
+  static_assert(kWaveLds >= kPredTile * sizeof(double), "the partial sums reuse the tables");
   const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int nw = (int)blockDim.x >> 6;
   float *const tab = (float *)(s_raw + w * kWaveLds);
   const size_t cb = blockIdx.y * chain_bytes;
   const char *prog = (const char *)prog0 + cb;
-  const int64_t tiles = (nt + 256 * W - 1) / (256 * W);
+  const int64_t tiles = (nt + kPredTile - 1) / kPredTile;
   const int64_t step = (int64_t)gridDim.x * (split > 1 ? 1 : nw);
   const int g0 = split > 1 ? (int)((int64_t)ngroups * w / split) : 0;
   const int g1 = split > 1 ? (int)((int64_t)ngroups * (w + 1) / split) : ngroups;
 
   for (int64_t tile = split > 1 ? blockIdx.x : (int64_t)blockIdx.x * nw + w; tile < tiles;
        tile += step) {
-    // byte offset of this lane's words in a predictor row (the first word
+    // byte offset of this lane's word in a predictor row (the first word
     // stands in past the last point)
-    int64_t at[W];
-    uint32_t vo[W];
-    const int64_t base = 256 * (int64_t)W * tile;
-#pragma unroll
-    for (int u = 0; u < W; ++u) {
-      at[u] = base + 256 * u + 4 * l;
-      vo[u] = at[u] < nt ? (uint32_t)(256 * u + 4 * l) : 0u;
-    }
+    const int64_t base = kPredTile * tile;
+    const int64_t at = base + 4 * l;
+    uint32_t vo = at < nt ? (uint32_t)(4 * l) : 0u;
     const uint8_t *X = Xt + base;
-    double acc[W][4];
-    float pend[W][4];  // leaf values read but not yet added
+    double acc[4];
+    float pend[4];  // leaf values read but not yet added
 #pragma unroll
-    for (int u = 0; u < W; ++u)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) acc[u][b] = 0.0, pend[u][b] = 0.f;
+    for (int b = 0; b < 4; ++b) acc[b] = 0.0, pend[b] = 0.f;
 
     struct Batch {
       uint32_t node[kPredBatch];
-      uint32_t x[kPredBatch][W];
+      uint32_t x[kPredBatch];
     };
     auto group = [&](int g) {
       return (cptr<PredGroup>)(prog + (size_t)g * sizeof(PredGroup));
@@ -239,36 +235,29 @@ __global__ void __launch_bounds__(1024)
       for (int e = 0; e < kPredBatch; ++e) B.node[e] = G->node[b * kPredBatch + e];
 #pragma unroll
       for (int e = 0; e < kPredBatch; ++e) {
-        // (32-bit lane offsets from a uniform row, kept that way)
-#pragma unroll
-        for (int u = 0; u < W; ++u) asm volatile("" : "+v"(vo[u]));
+        // (a 32-bit lane offset from a uniform row, kept that way)
+        asm volatile("" : "+v"(vo));
         const gptr<const uint8_t> xr = gbl(X) + (int64_t)(B.node[e] & 0xffffu) * ldx;
-#pragma unroll
-        for (int u = 0; u < W; ++u) B.x[e][u] = *(gptr<const u32_any>)(xr + vo[u]);
+        B.x[e] = *(gptr<const u32_any>)(xr + vo);
       }
     };
-    uint32_t code[W][4];
+    uint32_t code[4];
 #pragma unroll
-    for (int u = 0; u < W; ++u)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) code[u][b] = 0;
+    for (int b = 0; b < 4; ++b) code[b] = 0;
     auto process = [&](const Batch &B) {
 #pragma unroll
       for (int e = 0; e < kPredBatch; ++e) {
         const uint32_t node = B.node[e];
         const uint32_t cut = (node >> 16) & 0x1ffu;
-#pragma unroll
-        for (int u = 0; u < W; ++u) pred_decide4(code[u], B.x[e][u], cut);
+        pred_decide4(code, B.x[e], cut);
         if ((node >> 25) & 1u) {  // uniform
           const float *tt = tab + (node >> 26) * kPredTab;
 #pragma unroll
-          for (int u = 0; u < W; ++u)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              acc[u][b] += (double)pend[u][b];
-              pend[u][b] = tt[code[u][b]];
-              code[u][b] = 0;
-            }
+          for (int b = 0; b < 4; ++b) {
+            acc[b] += (double)pend[b];
+            pend[b] = tt[code[b]];
+            code[b] = 0;
+          }
         }
       }
     };
@@ -282,55 +271,41 @@ __global__ void __launch_bounds__(1024)
         if (n > 0) {
           // every node clears the leaves of its left subtree for a point that
           // goes right; the leaf is the leftmost one left
-          uint32_t v[W][4];
+          uint32_t v[4];
 #pragma unroll
-          for (int u = 0; u < W; ++u)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) v[u][b] = ~0u;
+          for (int b = 0; b < 4; ++b) v[b] = ~0u;
           for (int k = 0; k < n; ++k) {
             const uint32_t node = G->list[tr][2 * k], left = G->list[tr][2 * k + 1];
             const gptr<const uint8_t> xr = gbl(X) + (int64_t)(node & 0xffffu) * ldx;
             const uint32_t cut = node >> 16, keep = ~left;
+            const uint32_t x = *(gptr<const u32_any>)(xr + vo);
 #pragma unroll
-            for (int u = 0; u < W; ++u) {
-              const uint32_t x = *(gptr<const u32_any>)(xr + vo[u]);
-#pragma unroll
-              for (int b = 0; b < 4; ++b)
-                v[u][b] &= ((x >> (8 * b)) & 0xffu) >= cut ? keep : ~0u;
-            }
+            for (int b = 0; b < 4; ++b) v[b] &= ((x >> (8 * b)) & 0xffu) >= cut ? keep : ~0u;
           }
 #pragma unroll
-          for (int u = 0; u < W; ++u)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-              acc[u][b] += (double)tab[tr * kPredTab + (__ffs((int)v[u][b]) - 1)];
+          for (int b = 0; b < 4; ++b)
+            acc[b] += (double)tab[tr * kPredTab + (__ffs((int)v[b]) - 1)];
         } else {
           // Algorithm 1
           const int64_t j = (int64_t)g * kPredTrees + tr;
           const gptr<const uint16_t> ax = gbl((const uint16_t *)((const char *)axis0 + cb)) + j * H;
           const gptr<const uint8_t> ct = gbl(cut0 + cb) + j * H;
           const gptr<const float> lf = gbl((const float *)((const char *)leaf0 + cb)) + j * 2 * H;
-          int h[W][4];
+          int h[4];
 #pragma unroll
-          for (int u = 0; u < W; ++u)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) h[u][b] = 1;
+          for (int b = 0; b < 4; ++b) h[b] = 1;
           for (int lvl = 1; lvl < D; ++lvl)
 #pragma unroll
-            for (int u = 0; u < W; ++u)
+            for (int b = 0; b < 4; ++b) {
+              const int q = h[b] < H ? h[b] : 0;
+              const int cv = q ? ct[q] : 0;
+              const int a = ax[q] < p ? ax[q] : 0;
+              const bool in = at + b < nt;
+              const int xv = cv && in ? gbl(X)[(int64_t)a * ldx + vo + b] : 0;
+              if (cv) h[b] = 2 * h[b] + (xv >= cv ? 1 : 0);
+            }
 #pragma unroll
-              for (int b = 0; b < 4; ++b) {
-                const int q = h[u][b] < H ? h[u][b] : 0;
-                const int cv = q ? ct[q] : 0;
-                const int a = ax[q] < p ? ax[q] : 0;
-                const bool in = at[u] + b < nt;
-                const int xv = cv && in ? gbl(X)[(int64_t)a * ldx + vo[u] + b] : 0;
-                if (cv) h[u][b] = 2 * h[u][b] + (xv >= cv ? 1 : 0);
-              }
-#pragma unroll
-          for (int u = 0; u < W; ++u)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) acc[u][b] += (double)lf[h[u][b]];
+            for (int b = 0; b < 4; ++b) acc[b] += (double)lf[h[b]];
         }
       }
     };
@@ -370,12 +345,10 @@ __global__ void __launch_bounds__(1024)
       auto advance = [&]() -> bool {
         if (++b < nb) return true;
 #pragma unroll
-        for (int u = 0; u < W; ++u)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[u][q] += (double)pend[u][q];
-            pend[u][q] = 0.f;
-          }
+        for (int q = 0; q < 4; ++q) {
+          acc[q] += (double)pend[q];
+          pend[q] = 0.f;
+        }
         special(g);
         if (++g >= g1) return false;
         store_tab();
@@ -405,15 +378,12 @@ __global__ void __launch_bounds__(1024)
       }
     };
     if (split > 1) {
-      double *const part = (double *)tab;  // [W][4][64] of this wave
+      double *const part = (double *)tab;  // [4][64] of this wave
 #pragma unroll
-      for (int u = 0; u < W; ++u)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) part[(u * 4 + b) * 64 + l] = acc[u][b];
+      for (int b = 0; b < 4; ++b) part[b * 64 + l] = acc[b];
       __syncthreads();
-      for (int q = threadIdx.x; q < 256 * W; q += blockDim.x) {
-        // point q of the tile: lane (q / 4) mod 64 of word q / 256
-        const int k = ((q >> 8) * 4 + (q & 3)) * 64 + ((q >> 2) & 63);
+      for (int q = threadIdx.x; q < kPredTile; q += blockDim.x) {
+        const int k = (q & 3) * 64 + (q >> 2);  // point q of the tile: lane q / 4
         double s = 0.0;
         for (int v = 0; v < split; ++v) s += ((const double *)(s_raw + v * kWaveLds))[k];
         if (base + q < nt) emit(base + q, s);
@@ -421,10 +391,8 @@ __global__ void __launch_bounds__(1024)
       __syncthreads();
     } else {
 #pragma unroll
-      for (int u = 0; u < W; ++u)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          if (at[u] + b < nt) emit(at[u] + b, acc[u][b]);
+      for (int b = 0; b < 4; ++b)
+        if (at + b < nt) emit(at + b, acc[b]);
     }
   }
 }

@@ -1,8 +1,8 @@
 """Prediction by the compiled trees against the oracle's Algorithm 1: trees of
 every form of the program (no node, a decision table of up to 6 nodes, a leaf
 mask of up to 31, Algorithm 1 beyond), nodes left over below a leaf, ragged
-groups of 16 trees, point counts around the tile sizes, both tile widths and
-the split of the trees over waves, and predictor rows of any alignment.
+groups of 16 trees, point counts around the tile size, every split of the
+trees over waves, and predictor rows of any alignment.
 
 The sums are fp64 sums of f32 leaves; their order (tree by tree here, in
 parts there) moves them by at most m 2^-53 of the sum of magnitudes, so an f32
