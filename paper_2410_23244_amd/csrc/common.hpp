@@ -10,7 +10,8 @@ namespace bart {
 constexpr int kBlock = 512;           // threads per workgroup of the sweep kernel (256 VGPRs each)
 constexpr int kWaves = kBlock / 64;   // wave64 on CDNA4
 constexpr int kMaxLeaves = 128;       // leaves of a depth-8 heap tree
-constexpr int kStride = 144;          // 64-bit words per mailbox (>= kMaxLeaves + 1, 128-byte lines)
+constexpr int kStride = 144;          // 64-bit words per mailbox, in 128-byte lines
+static_assert(kStride >= kMaxLeaves + 2 && kStride * 8 % 128 == 0, "a sum per leaf and two counts");
 constexpr int kBinFloats = 32768;     // 128 KiB of LDS per-leaf bins
 constexpr int kMaxGrid = 256;         // mailboxes per buffer reserved in the workspace
 constexpr int kMaxLaunchSteps = (1 << 20) - 8;  // steps per launch (20-bit sequence numbers)

@@ -563,11 +563,11 @@ __device__ __forceinline__ void post(const SweepArgs *__restrict__ A, SH &sh, in
 // workgroup (polling thread i is thread kBlock - 64 ceil(nseg K / 64) + i):
 // the waves that build no rank table and compute no constants before the
 // gather, so they start polling soonest.  Returns nseg.  Ends with an LDS
-// barrier.
+// barrier.  The words are those from word `first_word` of a mailbox on.
 template <class SH>
 __device__ __forceinline__ int gather_polls(const SweepArgs *__restrict__ A, SH &sh, int par,
                                             uint32_t seq, int K, int nsum, uint32_t limit,
-                                            int clk = -1) {
+                                            int clk = -1, int first_word = 0) {
   const int G = A->G;
 #ifdef BART_PHASE_CLOCKS
   uint32_t poll_loads = 0;
@@ -576,7 +576,7 @@ __device__ __forceinline__ int gather_polls(const SweepArgs *__restrict__ A, SH 
     const int t = threadIdx.x;
     lds_barrier();  // the words were staged by the waves that formed them
     if (t < K) {
-      const uint64_t wv = sh.solo[t];
+      const uint64_t wv = sh.solo[first_word + t];
       double acc = 0.0;
       acc += t < nsum ? unpack_f64(wv) : (double)(wv & kPayloadMask);
       sh.part[t] = acc;
@@ -594,7 +594,7 @@ __device__ __forceinline__ int gather_polls(const SweepArgs *__restrict__ A, SH 
   if (t >= 0 && t < nseg * K) {
     const int k = t % K, seg = t / K;
     const int g0 = seg * span, g1 = min(G, g0 + span);
-    const uint64_t *base = A->pub + (int64_t)par * A->G * kStride + k;
+    const uint64_t *base = A->pub + (int64_t)par * A->G * kStride + first_word + k;
     double acc = 0.0;
 #pragma unroll 1
     for (int gb = g0; gb < g1; gb += 8) {
@@ -642,11 +642,13 @@ __device__ __forceinline__ double seg_total(const SH &sh, int nseg, int K, int k
   return acc;
 }
 
-// Grid-wide sum of one fp64 word per workgroup (sigma^2 step), into sh.tot[0].
+// Grid-wide sum of one fp64 word per workgroup (the sigma^2 step's, or a count
+// of the register kernel), into sh.tot[0].
 template <class SH>
 __device__ __forceinline__ void gather_total(const SweepArgs *__restrict__ A, SH &sh, int par,
-                                             uint32_t seq, int nsum, uint32_t limit) {
-  const int nseg = gather_polls(A, sh, par, seq, 1, nsum, limit);
+                                             uint32_t seq, int nsum, uint32_t limit,
+                                             int word = 0) {
+  const int nseg = gather_polls(A, sh, par, seq, 1, nsum, limit, -1, word);
   if (threadIdx.x == 0) sh.tot[0] = seg_total(sh, nseg, 1, 0);
   lds_barrier();
 }
@@ -1111,8 +1113,12 @@ __device__ __forceinline__ Gathered scalar(const Gathered &g) {
 // workgroups, 8 loads in flight; the subs of a wave are then added in
 // registers, and the wave's sums are one row of sh.part.  The number of
 // polling waves, 1, 2, 4 or 8, and so the order of every sum, depends on G
-// and K only: the fewest that leave a lane at most 8 workgroups.  Ends with
-// an LDS barrier, after which abort_flag is final for this step.
+// and K only: the fewest that leave a lane at most 8 workgroups, or all 8 where
+// none do (K > 16 on more than 128 workgroups, K > 32 on more than 64), whose
+// lanes then poll up to 32 workgroups in batches of 8.  K is the same for a
+// tree whether or not it is the first of a run of steps (whose own right-count
+// comes by gather_total), so where a launch starts changes no bit of a sum.
+// Ends with an LDS barrier, after which abort_flag is final for this step.
 template <class SH>
 __device__ __forceinline__ Gathered gather_rows(const SweepArgs *__restrict__ A, SH &sh, int par,
                                                 uint32_t seq, int K, uint32_t limit, int wv,
@@ -1761,16 +1767,12 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
       BART_CLOCK(clk, 2);
       // 3. the grid's sums of tree j and right-count of tree j+1, in the same
       //    order in every workgroup
-      const Gathered ga =
-          scalar(gather_rows(A, sh, par, seq, L + (first ? 2 : 1), Lc.spin_limit, wv, clk));
-      BART_CLOCK(clk, 3);
-      // set before the barrier of the gather only; read here, it is waited
-      // for together with the decision's words
-      const bool aborted = aborted_now();
       if (first) {
-        // the constants of the first tree, which no earlier step made
+        // the right-count and the constants of the first tree, which no earlier
+        // step made (in LDS from the barrier of the gather on)
+        gather_total(A, sh, par, seq, 1, Lc.spin_limit, L + 1);
         if (wv == kAcceptWave || wv == kConstWave) {
-          const double n_right = gathered(sh, ga, L + 1);
+          const double n_right = sh.tot[0];
           if (wv == kConstWave) {
             const ConstRegs c0 = load_const(A, c, h0, j, s, lane);
             draw_consts(A, sh, tconst(j), c, h0, j, s, c0, n_right);
@@ -1781,9 +1783,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
             accept_consts(A, sh, tconst(j), c, h0, h0.move() == kGrow ? (double)a - nr : (double)a, nr);
           }
         }
-        lds_barrier();
         first = false;
       }
+      const Gathered ga = scalar(gather_rows(A, sh, par, seq, L + 1, Lc.spin_limit, wv, clk));
+      BART_CLOCK(clk, 3);
+      // set before the barrier of the gather only; read here, it is waited
+      // for together with the decision's words
+      const bool aborted = aborted_now();
       double n_right1 = 0.0;  // read before the next sums replace it
       if ((wv == kAcceptWave || wv == kConstWave) && more1) n_right1 = gathered(sh, ga, L);
       const Decision d = decide_all(A, sh, c, tconst(j), h0, ga, wv == kStoreWave, tracing);

@@ -75,6 +75,41 @@ def test_runs_that_start_and_end_inside_a_sweep(m):
     _run(inp, 4, 5, [1, 1, 2, 3, 1, 4, m + 1, 5])
 
 
+@pytest.mark.parametrize("grid", [9, 17, 64, 245])
+def test_sums_do_not_depend_on_where_a_launch_starts(grid):
+    """A launch that starts inside a sweep adds every tree's partial sums in
+    the order of one that runs through: the same bits, for trees whose words
+    (with the first tree's extra one) lie on both sides of a layout's edge.
+    The residuals differ by up to 2^40 from workgroup to workgroup, and the
+    leaves stay too small to level them: partial sums of like size add up
+    exactly in fp64, in any order."""
+    from paper_2410_23244_amd.bart import BART_RESID_REGISTERS, from_inputs
+
+    per = 2048  # observations of a workgroup
+    inp = make_inputs(2, n=per * grid - 77, p=12, m=6, D=8)
+    inp.hyper.sigma_mu = 1e-12
+    one = from_inputs(inp, grid=grid, residency=BART_RESID_REGISTERS)
+    two = from_inputs(inp, grid=grid, residency=BART_RESID_REGISTERS)
+    for leaves in (6, 7, 8, 15, 31, 62, 63, 64, 100):
+        rng = np.random.default_rng(leaves)
+        st = _state(inp, leaves, rng)
+        scale = 2.0 ** rng.integers(0, 41, grid)
+        st["resid"] *= np.repeat(scale, per)[:inp.n].astype(np.float32)
+        one.set_state(st)
+        a = one.debug_steps(inp.m + 1, 5)
+        want = one.get_state()
+        for first in range(1, inp.m):
+            print(f"grid={grid} leaves={leaves} first={first}", flush=True)
+            two.set_state(st)
+            b = np.concatenate([two.debug_steps(first, 5), two.debug_steps(inp.m + 1 - first, 5)])
+            for f in ("sum", "log_r", "leaf_new", "ssr", "sigma2"):
+                np.testing.assert_array_equal(b[f], a[f], err_msg=f)
+            got = two.get_state()
+            for k in ("leaf", "resid", "idx", "cut"):
+                np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+    assert one.status() == 0 and two.status() == 0
+
+
 @pytest.mark.parametrize("n", [40003, 140003, 300007])
 def test_chunks_per_thread(n):
     # 1, 2 and 4 chunks per thread on at most 41 workgroups
