@@ -96,7 +96,9 @@ __device__ __forceinline__ constexpr int clock_slot(int) { return -1; }
   do {                  \
   } while (0)
 #endif
-constexpr int kNullRank = kMaxLeaves;  // rank of a padding point (slot 0): no bin, zero delta
+// rank of a padding point (slot 0): in no total, zero delta; so far above the
+// leaves that it is outside the register kernel's last bin pass too
+constexpr int kNullRank = kMaxLeaves + 31;
 constexpr int kBadRank = 255;          // rank of any other non-leaf slot: likewise, and flagged
 // proposal contexts: the streamed kernel has j (decide) to j+3 (load) in
 // flight, the register kernel j to j+4
@@ -221,7 +223,7 @@ struct Ctx {
   Prop pr;
   uint8_t rank_of[256];   // heap slot -> rank among larger-tree leaves (kNullRank: slot 0,
                           // kBadRank: another non-leaf)
-  uint8_t heap_of[256];   // rank -> heap slot; 0 from kNullRank on
+  uint8_t heap_of[256];   // rank -> heap slot; 0 from kMaxLeaves on
 };
 
 constexpr int kTabNodes = 6;
@@ -270,7 +272,7 @@ struct TreeConst {
 };
 
 struct Shared {
-  // its residual delta per rank: old value - new value; 0 from kNullRank on
+  // its residual delta per rank: old value - new value; 0 from kMaxLeaves on
   // (first: an LDS instruction's offset reaches it)
   float dlt[256];
   alignas(16) float bins[kBinFloats];
@@ -662,7 +664,7 @@ __device__ __noinline__ void trace_tree_step(bart_trace *R, Shared &sh, const Ct
   const int acc = sh.flags & 1, merged = (sh.flags >> 1) & 1;
   if (t < 256) {
     const int rnk = c.rank_of[t];
-    const bool in = rnk < kNullRank && t < 2 * H && c.heap_of[rnk] == t;  // a leaf of the larger tree
+    const bool in = rnk < kMaxLeaves && t < 2 * H && c.heap_of[rnk] == t;  // a leaf of the larger tree
     R->count[t] = in ? (int32_t)sh.cntd[rnk] : 0;
     R->sum[t] = in ? sh.S[rnk] : 0.0;
     float lv = 0.f;
@@ -1478,10 +1480,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
     sh.sigma2 = A->ctl->sigma2;
     sh.sd_unit = A->sigma_mu * sqrt(A->ctl->sigma2);
   }
-  // ranks from kNullRank on: zero delta, slot 0
-  if (t >= kNullRank && t < 256) sh.dlt[t] = 0.f;
-  for (int q = t; q < kRing * (256 - kNullRank); q += kBlock)
-    sh.ctx[q / (256 - kNullRank)].heap_of[kNullRank + q % (256 - kNullRank)] = 0;
+  // ranks from kMaxLeaves on: zero delta, slot 0
+  if (t >= kMaxLeaves && t < 256) sh.dlt[t] = 0.f;
+  for (int q = t; q < kRing * (256 - kMaxLeaves); q += kBlock)
+    sh.ctx[q / (256 - kMaxLeaves)].heap_of[kMaxLeaves + q % (256 - kMaxLeaves)] = 0;
   if (t < 6) sh.stats[t] = 0;
   int clk = -1;  // phase-clock slot of the current step (diagnostic build)
 
@@ -1524,7 +1526,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
 #pragma unroll
       for (int b = 0; b < 4; ++b) pk |= (uint32_t)c.rank_of[IC::get(rc, b)] << (8 * b);
       out[v] = pk;
-      static_assert(kBadRank == 255 && kNullRank == 128, "only kBadRank has its two top bits set");
+      static_assert(kBadRank == 255 && (kNullRank & 0xC0) == 0x80 && kMaxLeaves <= 128,
+                    "only kBadRank has its two top bits set");
       bad |= pk & (pk << 1);
     }
     if (h.move() == kGrow) {  // (a uniform branch; the bytes are loaded all the same)
@@ -1563,11 +1566,15 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   // 0, 2 go to set 0, those of 1, 3 to set 1; with four, position e to set
   // e), so each lane runs kSets independent chains of read-modify-writes,
   // for up to kRegRanks ranks at a time (a plain read-modify-write: LDS float
-  // atomics are many times slower; ranks outside the pass, the null rank of
-  // padding points among them, add 0 to a bin of the pass, so there is no
-  // branch per point); then a fixed-order fp64 reduction of the kSets x 8
-  // bins of each lane position and a DPP tree over the lanes; larger trees
-  // take several passes.  The wave that forms the total
+  // atomics are many times slower); then a fixed-order fp64 reduction of the
+  // kSets x 8 bins of each lane position and a DPP tree over the lanes; larger
+  // trees take several passes.  A lane has one bin more per set than a pass has
+  // ranks, which nothing reads: points outside the pass, and those without a
+  // leaf (the null and the bad rank), add to it, so a point needs no test and
+  // trees of every size one path.  (us a sweep at n = 1e6 / 1e5, ten at 1e3:
+  // 960 / 814 / 1,747; a test-free path for one pass beside a testing one 962
+  // / 824 / 1,792; with the points without a leaf tested in the waves that
+  // have any 975 / 827 / 1,804.)  The wave that forms the total
   // of rank k posts it as word k of this workgroup's mailbox for the step
   // that decides the tree (buffer par, step number seq), and after the first
   // bin barrier one thread posts the GROW right-count of tree + 1 as word L
@@ -1577,51 +1584,32 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
   // four sets with 8 chunks per thread (chains of 8 read-modify-writes
   // rather than 16: four chains 2547 -> 2562 chain-sweeps/s)
   constexpr int kSets = V >= 8 ? 4 : 2;
-  constexpr int kRegRanks = kBinFloats / (kSets * kBlock);  // 32 or 16
-  static_assert(kMaxLeaves % kRegRanks == 0 && kNullRank / kRegRanks >= kMaxLeaves / kRegRanks,
-                "the null rank must fall outside every bin pass");
+  constexpr int kRegBins = kBinFloats / (kSets * kBlock);  // 32 or 16 per lane and set
+  constexpr int kRegRanks = kRegBins - 1;
+  static_assert(kNullRank - (kMaxLeaves - 1) / kRegRanks * kRegRanks >= kRegRanks,
+                "points without a leaf go to the spare bin of every pass");
   auto reduce = [&](int tree, int L, const uint32_t (&rks)[V], int par, uint32_t seq, bool first) {
     const int wl = wv * 64 + lane;
     for (int base = 0; base < L; base += kRegRanks) {
-      // the bin of rank k is k mod kRegRanks; a point outside the pass adds
-      // 0 to its bin there (exact: a bin never holds -0).  Bins of different
-      // sets never share an address, so a pair (one point of each set) is
-      // read together and written together
-      if (mine && L <= kRegRanks) {
-        // one pass: a padding point adds its residual, 0, to some bin
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-#pragma unroll
-          for (int b0 = 0; b0 < 4; b0 += kSets) {
-            float *q[kSets];
-            float cur[kSets];
-#pragma unroll
-            for (int e = 0; e < kSets; ++e)
-              q[e] = sh.bins + ((((rks[v] >> (8 * (b0 + e))) & (uint32_t)(kRegRanks - 1)) * kSets + e) *
-                                    kBlock + wl);
-#pragma unroll
-            for (int e = 0; e < kSets; ++e) cur[e] = *q[e];
-#pragma unroll
-            for (int e = 0; e < kSets; ++e) *q[e] = cur[e] + r[v][b0 + e];
-          }
-      } else if (mine)
+      // the bin of rank k is k - base, the spare one outside the pass.  Bins
+      // of different sets never share an address, so a pair (one point of each
+      // set) is read together and written together
+      if (mine)
 #pragma unroll
       for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int b0 = 0; b0 < 4; b0 += kSets) {
-          const uint32_t pass = (uint32_t)(base / kRegRanks);
           int q[kSets];
-          float x[kSets], cur[kSets];
+          float cur[kSets];
 #pragma unroll
           for (int e = 0; e < kSets; ++e) {
-            const uint32_t rr = (rks[v] >> (8 * (b0 + e))) & 0xffu;
-            q[e] = ((int)(rr % kRegRanks) * kSets + e) * kBlock + wl;
-            x[e] = rr / kRegRanks == pass ? r[v][b0 + e] : 0.f;
+            const uint32_t in_pass = ((rks[v] >> (8 * (b0 + e))) & 0xffu) - (uint32_t)base;
+            q[e] = ((int)min(in_pass, (uint32_t)kRegRanks) * kSets + e) * kBlock + wl;
           }
 #pragma unroll
           for (int e = 0; e < kSets; ++e) cur[e] = sh.bins[q[e]];
 #pragma unroll
-          for (int e = 0; e < kSets; ++e) sh.bins[q[e]] = cur[e] + x[e];
+          for (int e = 0; e < kSets; ++e) sh.bins[q[e]] = cur[e] + r[v][b0 + e];
         }
       if (base == 0) BART_CLOCK(clk, 9);
       lds_barrier();
@@ -1821,7 +1809,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs *__restrict__ A, cons
           bool touch = false;
           ChunkT out = 0;
           // every rank's heap slot read unconditionally (no exec mask per
-          // point; ranks from kNullRank on have slot 0), then selected
+          // point; ranks from kMaxLeaves on have slot 0), then selected
           int hs[4];
 #pragma unroll
           for (int b = 0; b < 4; ++b) hs[b] = c.heap_of[(rk[v] >> (8 * b)) & 0xff];
@@ -2002,10 +1990,10 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
     sh.nr[0] = sh.nr[1] = 0;
     sh.sigma2 = A->ctl->sigma2;
   }
-  // ranks from kNullRank on: zero delta, slot 0
-  if (t >= kNullRank && t < 256) sh.dlt[t] = 0.f;
-  for (int q = t; q < kRing * (256 - kNullRank); q += kBlock)
-    sh.ctx[q / (256 - kNullRank)].heap_of[kNullRank + q % (256 - kNullRank)] = 0;
+  // ranks from kMaxLeaves on: zero delta, slot 0
+  if (t >= kMaxLeaves && t < 256) sh.dlt[t] = 0.f;
+  for (int q = t; q < kRing * (256 - kMaxLeaves); q += kBlock)
+    sh.ctx[q / (256 - kMaxLeaves)].heap_of[kMaxLeaves + q % (256 - kMaxLeaves)] = 0;
   if (t < 6) sh.stats[t] = 0;
   int uncounted = -1;  // tree step whose move statistics workgroup 0 has yet to count
 
@@ -2078,8 +2066,8 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
     // a point of a GROW's eta goes right exactly when its rank is that of
     // the right child (every other slot has another rank), so the GROW
     // right-count is the number of bytes of the packed ranks equal to it;
-    // without a GROW, a byte no rank takes (ranks: below kNullRank, or
-    // kBadRank)
+    // without a GROW, a byte no rank takes (ranks: below kMaxLeaves, kNullRank
+    // or kBadRank)
     static_assert(kNullRank < 254 && kBadRank != 254, "254 must be no rank");
     const uint32_t right4 = (uint32_t)(xn ? cn.rank_of[2 * eta_n + 1] : 254) * 0x01010101u;
     const int cut_a = ca.pr.cut, grow_a = do_a && ca.pr.move == kGrow ? eta_a : -1;
@@ -2381,7 +2369,7 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
           ChunkT out = 0;
           if (changed) {
             // every rank's heap slot read unconditionally (no exec mask per
-            // point; ranks from kNullRank on have slot 0), then selected
+            // point; ranks from kMaxLeaves on have slot 0), then selected
             int hs[4];
 #pragma unroll
             for (int b = 0; b < 4; ++b) hs[b] = ca.heap_of[(rk >> (8 * b)) & 0xff];

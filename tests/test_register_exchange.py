@@ -110,6 +110,39 @@ def test_sums_do_not_depend_on_where_a_launch_starts(grid):
     assert one.status() == 0 and two.status() == 0
 
 
+@pytest.mark.parametrize("grid,V", [(3, 1), (1, 8)])
+@pytest.mark.parametrize("slot", [0, 255])
+def test_bad_entries_stay_out_of_the_sums(slot, grid, V):
+    """An observation whose index entry is no leaf (0, or a slot outside its
+    tree) is reported and takes no part in any leaf's sum: the other points'
+    sums and leaves do not depend on its residual.  Trees of few leaves come
+    before trees of as many as a bin pass holds."""
+    from paper_2410_23244_amd.bart import BART_RESID_REGISTERS, from_inputs
+
+    inp = make_inputs(2, n={1: 4999, 8: 16001}[V], p=30, m=6, D=8)
+    runs = []
+    for resid in (0.0, 1000.0):
+        g = from_inputs(inp, grid=grid, residency=BART_RESID_REGISTERS)
+        assert g.launch_info().chunks_per_thread == V
+        parts = [_state(inp, k, np.random.default_rng(k)) for k in (4, 16, 32)]
+        st = dict(parts[0])
+        for k in ("axis", "cut", "leaf", "idx"):
+            st[k] = np.concatenate([q[k][:2] for q in parts])
+        st["resid"] = parts[0]["resid"].copy()
+        i = 1234
+        st["idx"][:, i] = slot
+        st["resid"][i] = resid
+        print(f"slot={slot} V={V} resid={resid}", flush=True)
+        g.set_state(st)
+        runs.append((g.debug_steps(inp.m, 7), g.get_state(), g.status()))
+    (a, sa, bits), (b, sb, _) = runs
+    assert bits & 2
+    for f in ("sum", "leaf_new", "accept", "count"):
+        np.testing.assert_array_equal(a[f], b[f], err_msg=f)
+    np.testing.assert_array_equal(np.delete(sa["resid"], i), np.delete(sb["resid"], i))
+    assert sb["resid"][i] == 1000.0
+
+
 @pytest.mark.parametrize("n", [40003, 140003, 300007])
 def test_chunks_per_thread(n):
     # 1, 2 and 4 chunks per thread on at most 41 workgroups
