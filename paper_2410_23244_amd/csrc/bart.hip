@@ -504,7 +504,6 @@ void launch_predict(bart_handle *h, const uint8_t *Xt, int64_t ldx, int64_t nt, 
   const size_t cb = h->lay.chain_bytes;
   k_pred_program<<<dim3(ngroups, h->nchain), 64 * kPredTrees, 0, h->stream>>>(
       axis, cut, leaf, prog, m, p, D, h->H, cb);
-  constexpr int64_t kWaveLds = kPredTrees * kPredTab * sizeof(float);
   // Four waves of a block share a tile's groups of trees wherever there are
   // as many: a wave's batches are one chain of loads, and short chains over
   // more tiles in flight keep the vector units busier than a tile per wave
@@ -513,16 +512,21 @@ void launch_predict(bart_handle *h, const uint8_t *Xt, int64_t ldx, int64_t nt, 
   // and a tile per wave 103, 106, 118 and 258).  Up to 16 while the launch has
   // fewer than 8 waves per compute unit (1e5 points, 4 / 8 waves: 25 / 21;
   // 1,000 trees of depth 8 122 / 86, and on inputs not in the caches 89 with 8
-  // against 97 with 16).
+  // against 97 with 16).  A wave takes at most two of the ranges that fix the
+  // order of a sum: a third to hold cost a quarter of the waves in flight
+  // (400 trees, 1e6 points: 222 with 4 waves a tile, 180 with 8).
   const int64_t tiles = (nt + kPredTile - 1) / kPredTile;
+  const int ranges = pred_ranges(ngroups);
   int split = 1;
-  while (split < 16 && 2 * split <= ngroups &&
-         (split < 4 || tiles * h->nchain * split < 8 * (int64_t)h->cus))
+  while (2 * split <= ranges &&
+         (split < 4 || 2 * split < ranges || tiles * h->nchain * split < 8 * (int64_t)h->cus))
     split *= 2;
   const int nw = split > 1 ? split : 4;
-  k_pred_eval<ACC><<<dim3(grid_for(tiles, split > 1 ? 1 : 4), h->nchain), 64 * nw, nw * kWaveLds,
-                     h->stream>>>(Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups, D, h->H, offset,
-                                  cb, split, out, sum, sumsq);
+  const int per_wave = ranges / split;
+  k_pred_eval<ACC><<<dim3(grid_for(tiles, split > 1 ? 1 : 4), h->nchain), 64 * nw,
+                     nw * pred_wave_lds(per_wave), h->stream>>>(
+      Xt, ldx, nt, p, prog, axis, cut, leaf, ngroups, D, h->H, offset, cb, split, per_wave,
+      31 - __builtin_clz((unsigned)ranges), out, sum, sumsq);
 }
 
 }  // namespace

@@ -180,11 +180,28 @@ __device__ __forceinline__ void pred_decide4(uint32_t (&code)[4], uint32_t x, ui
 // The compiled trees at a tile of 64 x 4 points per wave: lane l's word holds
 // the 4 points at 4 (64 tile + l).  split = 1: every wave has a tile of its
 // own.  Else the waves of a block share one tile and the groups of trees, in
-// order, among them, and their fp64 sums are added in that order.
-// blockIdx.y = chain.  ACC: add f and f^2 (fp64) to sum and sumsq instead of
+// order, among them.  The groups are cut into `ranges` ranges, a power of two
+// that the number of groups fixes (pred_ranges), `per_wave` of them for each
+// of the waves; a range is summed in fp64 in
+// order, and the ranges by a binary tree, of which a wave makes the part over
+// its own: the split, which is chosen by the number of points and chains,
+// changes no bit of a sum.  blockIdx.y = chain.  ACC: add f and f^2 (fp64) to sum and sumsq instead of
 // writing fp32(f) to out.  What bounds it is the issue of the decisions, two
 // instructions each per point, then the words' loads: 1e6 points, 200 trees,
 // 402 us by Algorithm 1, 90 us here.
+constexpr int kPredRanges = 16;  // most ranges, and most waves that share a tile
+constexpr int pred_ranges(int ngroups) {
+  int r = 1;
+  while (r < kPredRanges && 2 * r <= ngroups) r *= 2;
+  return r;
+}
+// LDS of a wave with 1 or 2 ranges: the tables of a group (its fp64 sums in
+// their place at the end), and the sums of the first of two
+constexpr int kPredSums = kPredTile * sizeof(double);
+__host__ __device__ constexpr int pred_wave_lds(int per_wave) {
+  return kPredTrees * kPredTab * (int)sizeof(float) + (per_wave > 1 ? kPredSums : 0);
+}
+
 typedef uint32_t u32_any __attribute__((aligned(1)));  // Xt has no alignment of its own
 template <class T>
 using cptr = const __attribute__((address_space(4))) T *;  // scalar loads
@@ -193,21 +210,25 @@ template <bool ACC>
 __global__ void __launch_bounds__(1024)
     k_pred_eval(const uint8_t *Xt, int64_t ldx, int64_t nt, int p, const PredGroup *prog0,
                 const uint16_t *axis0, const uint8_t *cut0, const float *leaf0, int ngroups, int D,
-                int H, double offset, size_t chain_bytes, int split, float *out0, double *sum0,
-                double *sumsq0) {
+                int H, double offset, size_t chain_bytes, int split, int per_wave, int lg_ranges,
+                float *out0, double *sum0, double *sumsq0) {
   extern __shared__ __align__(16) char s_raw[];
-  constexpr size_t kWaveLds = kPredTrees * kPredTab * sizeof(float);  // also 64 x 4 fp64
-  static_assert(kWaveLds >= kPredTile * sizeof(double), "the partial sums reuse the tables");
+  static_assert(kPredTrees * kPredTab * sizeof(float) >= kPredSums,
+                "the partial sums reuse the tables");
+  const int wave_lds = pred_wave_lds(per_wave);
   const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int nw = (int)blockDim.x >> 6;
-  float *const tab = (float *)(s_raw + w * kWaveLds);
+  float *const tab = (float *)(s_raw + w * wave_lds);
+  double *const held = (double *)(tab + kPredTrees * kPredTab);  // [4][64]
   const size_t cb = blockIdx.y * chain_bytes;
   const char *prog = (const char *)prog0 + cb;
   const int64_t tiles = (nt + kPredTile - 1) / kPredTile;
   const int64_t step = (int64_t)gridDim.x * (split > 1 ? 1 : nw);
-  const int g0 = split > 1 ? (int)((int64_t)ngroups * w / split) : 0;
-  const int g1 = split > 1 ? (int)((int64_t)ngroups * (w + 1) / split) : ngroups;
+  const int r0 = split > 1 ? w * per_wave : 0;  // its first range
+  auto range_start = [&](int r) { return (int)((uint32_t)ngroups * (uint32_t)r >> lg_ranges); };
+  const int g0 = range_start(r0), g1 = range_start(r0 + per_wave);
+  const int mid = per_wave > 1 ? range_start(r0 + 1) : 0;  // start of its second range
 
   for (int64_t tile = split > 1 ? blockIdx.x : (int64_t)blockIdx.x * nw + w; tile < tiles;
        tile += step) {
@@ -350,7 +371,13 @@ __global__ void __launch_bounds__(1024)
           pend[q] = 0.f;
         }
         special(g);
-        if (++g >= g1) return false;
+        if (++g == mid)  // its first range is summed: held until the second is
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            held[q * 64 + l] = acc[q];
+            acc[q] = 0.0;
+          }
+        if (g >= g1) return false;
         store_tab();
         if (g + 1 < g1) fetch_tab(g + 1);
         b = 0;
@@ -365,6 +392,9 @@ __global__ void __launch_bounds__(1024)
         process(B1);
         if (!advance()) break;
       }
+      if (mid)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = held[q * 64 + l] + acc[q];
     }
 
     auto emit = [&](int64_t i, double s) {
@@ -384,8 +414,14 @@ __global__ void __launch_bounds__(1024)
       __syncthreads();
       for (int q = threadIdx.x; q < kPredTile; q += blockDim.x) {
         const int k = (q & 3) * 64 + (q >> 2);  // point q of the tile: lane q / 4
-        double s = 0.0;
-        for (int v = 0; v < split; ++v) s += ((const double *)(s_raw + v * kWaveLds))[k];
+        auto two = [&](int v) {
+          return ((const double *)(s_raw + v * wave_lds))[k] +
+                 ((const double *)(s_raw + (v + 1) * wave_lds))[k];
+        };
+        auto four = [&](int v) { return two(v) + two(v + 2); };
+        double s = split > 2 ? four(0) : two(0);
+        if (split > 4) s += four(4);
+        if (split > 8) s += four(8) + four(12);
         if (base + q < nt) emit(base + q, s);
       }
       __syncthreads();

@@ -99,3 +99,51 @@ def test_tiles_and_splits(nt, nchain, m):
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_rows_of_any_alignment(shift):
     _check(20, 6, 7, 1003, 1, np.full(20, 0.6), 5, shift)
+
+
+@pytest.mark.parametrize("m,D", [(5, 6), (17, 6), (40, 8), (64, 6), (100, 6), (130, 8), (300, 6),
+                                 (1000, 6)])
+def test_sums_do_not_depend_on_the_batch(m, D):
+    """The fp64 sum of a point is added in one order, whatever the number of
+    points, their place in the batch and the number of chains (and so the
+    number of waves that share a tile's trees): the same bits.  The leaves
+    differ by up to 2^40, as f32 values of like size add up exactly in fp64,
+    in any order."""
+    import torch
+
+    from paper_2410_23244_amd import bart as B
+
+    rng = np.random.default_rng(m)
+    p, few, nt = 11, 64, 150001
+    Xt = torch.from_numpy(rng.integers(0, 256, (p, B.x_stride_for(nt))).astype(np.uint8)).cuda()
+    axis, cut, leaf = _forest(rng, m, D, p, np.full(m, 0.6))
+    leaf *= (2.0 ** rng.integers(-20, 21, leaf.shape)).astype(np.float32)
+    handles = []
+    for nchain in (1, 4):
+        g = B.Bart(np.zeros((p, few), np.uint8), np.zeros(few, np.float32),
+                   np.full(p, 255, np.int32), ntree=m, max_depth=D, nchain=nchain)
+        idx = np.empty((m, few), np.uint8)
+        for j in range(m):
+            h = 1
+            while h < cut.shape[1] and cut[j, h]:
+                h = 2 * h  # bin 0 is below every cut
+            idx[j] = h
+        for c in range(nchain):
+            g.set_state(dict(axis=axis, cut=cut, leaf=leaf, idx=idx,
+                             resid=np.zeros(few, np.float32), sigma2=1.0, sweep=0), c)
+        handles.append(g)
+
+    def f(g, first, n):
+        s = torch.zeros((g.nchain, n), dtype=torch.float64, device="cuda")
+        s2 = torch.zeros_like(s)
+        print(f"m={m} D={D} nchain={g.nchain} first={first} n={n}", flush=True)
+        B.bart_predict_accumulate(g.h, Xt.data_ptr() + first, Xt.shape[1], n, 0.1, s.data_ptr(),
+                                  s2.data_ptr())
+        return s.cpu().numpy()
+
+    want = f(handles[0], 0, nt)[0]
+    for g in handles:
+        for first, n in ((0, 100), (0, 4001), (0, 60001), (0, 100003), (777, 3001)):
+            got = f(g, first, n)
+            for c in range(g.nchain):
+                np.testing.assert_array_equal(got[c], want[first:first + n])
