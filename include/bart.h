@@ -246,8 +246,9 @@ int bart_posterior_summary(bart_handle *h, const double *sum, const double *sums
 /* Sum-of-trees prediction f(x) = offset + sum_j g(x; T_j, M_j) (eq. bartdef),
  * each tree's leaf that of Algorithm 1, summed in fp64 and rounded to f32, for
  * every chain.  The order of the sum is fixed by the chain's trees alone: a
- * point's f has the same bits in every batch, beside any number of chains.  Xt: device u8 [p][xt_stride] binned like
- * X_b, xt_stride >= n_t and a multiple of 16; out: device f32 [nchain][n_t]. */
+ * point's f has the same bits in every batch, beside any number of chains.  Xt:
+ * device u8 [p][xt_stride] binned like X_b, xt_stride >= n_t and a multiple of
+ * 16; out: device f32 [nchain][n_t]. */
 int bart_predict(bart_handle *h, const uint8_t *Xt, int64_t xt_stride, int64_t n_t,
                  double offset, float *out);
 
