@@ -248,7 +248,11 @@ int bart_posterior_summary(bart_handle *h, const double *sum, const double *sums
  * every chain.  The order of the sum is fixed by the chain's trees alone: a
  * point's f has the same bits in every batch, beside any number of chains.  Xt:
  * device u8 [p][xt_stride] binned like X_b, xt_stride >= n_t and a multiple of
- * 16; out: device f32 [nchain][n_t]. */
+ * 16; out: device f32 [nchain][n_t].  The call writes the compiled trees into
+ * the workspace before it reads them: a thread may predict while another steps
+ * the handle (each prediction is of the trees between two calls), but a
+ * prediction captured into a graph and replayed on another stream must not run
+ * beside calls that change the trees. */
 int bart_predict(bart_handle *h, const uint8_t *Xt, int64_t xt_stride, int64_t n_t,
                  double offset, float *out);
 

@@ -380,6 +380,9 @@ struct bart_handle {
   std::vector<int32_t> n_cuts, nz_list, nz_rank;
   SweepFn fn;
   uint64_t *scratch_dev;  // device address of this device's scratch array
+  // held while a call enqueues kernels that read or write the trees together
+  // (a prediction's two): another thread's step must not come between them
+  std::mutex enqueue;
 };
 
 namespace {
@@ -446,6 +449,7 @@ int launch_sweep(bart_handle *h, int32_t n_steps, uint64_t seed, bart_trace *tra
                  int64_t trace_stride, bool in_scratch, uint32_t spin_limit = kSpinLimit,
                  int32_t absent_wg = -1) {
   HIP_TRY(hipSetDevice(h->device));
+  std::lock_guard<std::mutex> lk(h->enqueue);
   // mailbox words carry launch-relative step numbers: clear both buffers of
   // every chain (a fill kernel, so the call can be captured into a graph)
   const int64_t words = 2 * (int64_t)h->G * kStride;
@@ -495,6 +499,7 @@ int run_steps(bart_handle *h, int64_t steps, uint64_t seed, bart_trace *trace,
 template <bool ACC>
 void launch_predict(bart_handle *h, const uint8_t *Xt, int64_t ldx, int64_t nt, double offset,
                     float *out, double *sum, double *sumsq) {
+  std::lock_guard<std::mutex> lk(h->enqueue);
   const int m = h->cfg.ntree, p = h->cfg.p, D = h->cfg.max_depth;
   const int ngroups = (m + kPredTrees - 1) / kPredTrees;
   const uint16_t *axis = atc<uint16_t>(h, 0, h->lay.axis);
@@ -824,6 +829,7 @@ int bart_set_state(bart_handle *h, const bart_state *s) {
   if (s->sweep < 0 || s->next < 0 || s->next > c.ntree) return fail(BART_EINVAL, "bad position");
   if (c.probit && !s->latent) return fail(BART_EINVAL, "a probit state needs its latents");
   HIP_TRY(hipSetDevice(h->device));
+  std::lock_guard<std::mutex> lk(h->enqueue);
   const size_t m = c.ntree, H = h->H;
   hipStream_t st = h->stream;
   const Layout &L = h->lay;
