@@ -36,9 +36,9 @@
 // owner workgroup (j mod G) and read by all in the next sweep; the sigma^2
 // step publishes them with release/acquire fences.
 // What bounds a step at these sizes is neither bandwidth nor the exchange's
-// load latency alone but the instructions a wave runs one after the other:
-// about 1,000 per wave and tree step at n = 1e6, 2 waves per SIMD, I-cache
-// misses none, half of the wave cycles waiting.  So work is taken out of the
+// load latency alone but the instructions a wave runs one after the other
+// (counted before every wave took the decision: about 1,000 per wave and tree
+// step at n = 1e6, 2 waves per SIMD, half of the wave cycles waiting).  So work is taken out of the
 // waves' common path, or done for 4 points in one word.
 #pragma once
 #include "common.hpp"
@@ -2191,7 +2191,7 @@ __device__ __forceinline__ void sweep_body_stream(const SweepArgs *__restrict__ 
         // point, and the leaf that Algorithm 1 reaches by these decisions from
         // the tree's table (two instructions per decision and a table read,
         // where masks and a descent in registers took about 4 per decision
-        // and 30 per point: n = 1e6 2,050 -> 1,870 us a sweep, n = 5e6 1,677
+        // and 30 per point: n = 1e6 2,050 -> 1,890 us a sweep, n = 5e6 1,677
         // -> 1,351; six nodes cover nearly all trees the sampler grows, and
         // each more doubles the table)
         uint32_t cu[U], code[U][4], wd[kTabNodes][U];
