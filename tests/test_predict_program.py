@@ -147,3 +147,54 @@ def test_sums_do_not_depend_on_the_batch(m, D):
             got = f(g, first, n)
             for c in range(g.nchain):
                 np.testing.assert_array_equal(got[c], want[first:first + n])
+
+
+def test_predictions_beside_steps():
+    """A thread that predicts while another steps the handle gets the trees of
+    one state, never the tables of one and the large trees of the next."""
+    import threading
+
+    import torch
+
+    from paper_2410_23244_amd import bart as B
+    from paper_2410_23244_amd.inputs import make_inputs
+    from tests.test_register_exchange import _state
+
+    inp = make_inputs(2, n=600, p=12, m=24, D=8)
+    sweeps, seed, nt = 200, 3, 4000
+    parts = [_state(inp, k, np.random.default_rng(k)) for k in (4, 40)]
+    st = dict(parts[0])
+    for k in ("axis", "cut", "leaf", "idx"):
+        st[k] = np.concatenate([q[k][:12] for q in parts])
+    rng = np.random.default_rng(1)
+    Xt = torch.from_numpy(rng.integers(0, 256, (inp.p, B.x_stride_for(nt))).astype(np.uint8)).cuda()
+
+    def f(g):
+        out = torch.empty(nt, dtype=torch.float32, device="cuda")
+        B.bart_predict(g.h, Xt.data_ptr(), Xt.shape[1], nt, 0.0, out.data_ptr())
+        return out
+
+    a, b = B.from_inputs(inp), B.from_inputs(inp)
+    a.set_state(st)
+    b.set_state(st)
+    states = [f(a).cpu().numpy()]
+    for _ in range(sweeps):
+        a.step(1, seed)
+        states.append(f(a).cpu().numpy())
+    outs, stop = [], threading.Event()
+
+    def predict():
+        while not stop.is_set() and len(outs) < 20000:
+            outs.append(f(b))
+
+    th = threading.Thread(target=predict)
+    th.start()
+    for _ in range(sweeps):
+        b.step(1, seed)
+    stop.set()
+    th.join()
+    torch.cuda.synchronize()
+    known = {s.tobytes() for s in states}
+    bad = sum(o.cpu().numpy().tobytes() not in known for o in outs)
+    print(f"{len(outs)} predictions beside {sweeps} sweeps, {bad} of no state", flush=True)
+    assert outs and bad == 0 and b.status() == 0
