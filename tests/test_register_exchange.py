@@ -143,9 +143,17 @@ def test_bad_entries_stay_out_of_the_sums(slot, grid, V):
     assert sb["resid"][i] == 1000.0
 
 
-@pytest.mark.parametrize("n", [40003, 140003, 300007])
-def test_chunks_per_thread(n):
-    # 1, 2 and 4 chunks per thread on at most 41 workgroups
-    inp = make_inputs(2, n=n, p=20, m=5, D=6)
-    grid = {40003: 20, 140003: 35, 300007: 41}[n]
-    _run(inp, grid, 9, [inp.m + 1])
+@pytest.mark.parametrize("n,grid,V", [(40003, 20, 1), (140003, 35, 2), (300007, 41, 4),
+                                      (39711, 20, 1), (140063, 35, 2), (295711, 41, 4),
+                                      (295711, 20, 8)])
+def test_chunks_per_thread(n, grid, V):
+    # 1, 2, 4 and 8 chunks per thread; with the last four sizes the last
+    # workgroup that has points has them in 4 of its 8 waves.  Leaves on both
+    # sides of a bin pass (31 ranks, 15 with 8 chunks per thread)
+    from paper_2410_23244_amd.bart import BART_RESID_REGISTERS, from_inputs
+
+    inp = make_inputs(2, n=n, p=20, m=5, D=8)
+    info = from_inputs(inp, grid=grid, residency=BART_RESID_REGISTERS).launch_info()
+    assert (info.chunks_per_thread, info.grid) == (V, grid)
+    for leaves in {1: [9], 2: [9, 30, 31, 32], 4: [9, 30, 31, 32], 8: [14, 15, 16, 33]}[V]:
+        _run(inp, grid, leaves, [inp.m + 1])
